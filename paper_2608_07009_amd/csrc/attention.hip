@@ -28,6 +28,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fetch_device.h"
 
@@ -41,7 +42,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunk = 32;            // tokens per wave per iteration
 constexpr int kTargetWorkgroups = 256;
-constexpr int kMaxSplitRecords = 1024;  // record indices of one split staged in LDS
+constexpr int kMaxSplitRecords = 2048;  // record indices of one split staged in LDS
 // Rescale the running output only when a head's running max grows by more than this (log2
 // units): exponentials are taken against a slightly stale max (values up to 2^8), which is
 // exact softmax arithmetic with a different reference point and keeps fp32/bf16 far from
@@ -65,6 +66,7 @@ struct AttnArgs {
   const int32_t* idx;
   float* part_o;    // [units][n_parts][H][DV]
   float2* part_ml;  // [units][n_parts][H] (running max in log2 units, running sum)
+  float* out;       // [units][H][DV]: the output, for the kernels that write it themselves
   int64_t rec_per_unit;
   int32_t R, token_bytes, tpr_shift, k, H, n_tok;
   int32_t split_tokens, n_wg_splits, hb, n_parts, n_wg;
@@ -98,15 +100,18 @@ __device__ __host__ inline int64_t mla_part_offset(int head, int dim) {
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// Two softmax weights 2^(s0 - m), 2^(s1 - m) rounded to bf16 (nearest even, one packed
-// v_cvt_pk_bf16_f32), the first in the low half; *psum accumulates the rounded values in that
-// order. The exponential is the hardware v_exp_f32: weights below 2^-126 flush to zero.
-__device__ inline uint32_t weights_bf16x2(float s0, float s1, float m, float* psum) {
-  const f32x2 e = {__builtin_amdgcn_exp2f(s0 - m), __builtin_amdgcn_exp2f(s1 - m)};
-  const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(e, bf16x2_t));
-  *psum += __uint_as_float(w << 16);
-  *psum += __uint_as_float(w & 0xFFFF0000u);
-  return w;
+// Two softmax weights 2^(s0 scale - m), 2^(s1 scale - m) rounded to bf16 (nearest even, one
+// packed v_cvt_pk_bf16_f32), the first in the low half. The exponential is the hardware
+// v_exp_f32: weights below 2^-126 flush to zero.
+__device__ inline uint32_t weights_bf16x2(float s0, float s1, float scale, float m) {
+  const f32x2 e = {__builtin_amdgcn_exp2f(__builtin_fmaf(s0, scale, -m)),
+                   __builtin_amdgcn_exp2f(__builtin_fmaf(s1, scale, -m))};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(e, bf16x2_t));
+}
+// sum + both (rounded) weights of w.
+__device__ inline float add_weights(uint32_t w, float sum) {
+  const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w), ones, sum, false);
 }
 __device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
@@ -125,15 +130,27 @@ typedef __attribute__((address_space(3))) void lds_void;
 __device__ inline uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const lds_void*)p;
 }
-__device__ inline u32x4 lds_read_b128(uint32_t addr) {
+template <int OFF>
+__device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "immediate offset");
   u32x4 v;
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
   return v;
 }
-__device__ inline v4i16 lds_read_tr16_b64(uint32_t addr) {
+template <int OFF>
+__device__ __forceinline__ v4i16 lds_read_tr16_b64(uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "immediate offset");
   v4i16 v;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(v) : "v"(addr));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
   return v;
+}
+// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant (immediate offsets).
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
 }
 // Wait until at most N LGKM operations are outstanding; a and b are the registers of the reads
 // waited for (tied, so that their users stay after the wait).
@@ -141,14 +158,9 @@ template <int N>
 __device__ __forceinline__ void lgkm_wait2(v4i16& a, v4i16& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
-// The same for two 16-byte reads, with n (a constant once the caller's loop is unrolled, at
-// most M) selecting the count.
-template <int M>
-__device__ __forceinline__ void lgkm_wait2_upto(int n, u32x4& a, u32x4& b) {
-  if constexpr (M >= 0) {
-    if (n == M) asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(M));
-    else lgkm_wait2_upto<M - 1>(n, a, b);
-  }
+template <int N>
+__device__ __forceinline__ void lgkm_wait2(u32x4& a, u32x4& b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 // S^T += K . Q^T for one k-step once the K rows' read (with at most N later LDS reads) is in;
 // the first step of a chain (FIRST) starts from zero. The s_nop covers the wait states after a
@@ -172,95 +184,97 @@ __device__ inline void wait_loads_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// LDS tile of one 32-token chunk: token t's 16-byte piece c at slot t * PP + c, PP >= P pieces
-// per row. The padding makes consecutive rows start 36 (MLA: PP = 73) or 20 (GQA: PP = 37)
-// banks apart, so the 16 rows read by one MFMA operand load hit distinct banks, and the
-// transpose reads (4 rows x 4 column pairs per 16 lanes) do too.
+// Every LDS write of this wave (and any LDS read) done, then the workgroup synchronised; loads
+// stay in flight.
+__device__ inline void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// LDS tile of 32 rows (a chunk's tokens, or 32 query rows) of P 16-byte pieces, P a multiple of
+// 8: blocks of 8 rows x 8 pieces (128 bytes of each row), 1 KB each, block (row group, segment)
+// at (rg * NSEG + seg) * 1024. One 64-lane direct global->LDS load fills one block, 8 lanes per
+// row: each group of 8 lanes reads one 128-byte run of its row, and a lane needs one global
+// address per row group, the segment being an immediate offset (an earlier layout of padded rows
+// spent 18 vector instructions per load on finding each lane's row, and its loads straddled
+// rows: 64 units of 16 heads took 81 us that way, 39 this way). Inside a block, piece p
+// of row r sits in 16-byte slot p ^ tile_swizzle(r): any 16 consecutive rows then place the same
+// piece in 16 different slots of the 256 bytes that all 64 banks serve (row parity picks the
+// half), and so do the transpose reads' row sets.
 template <int P>
-struct TileRow {
-  static constexpr int PP = (P == 72) ? 73 : (P == 32 ? 37 : P + 1);
+struct Tile {
+  static_assert(P % 8 == 0, "whole 128-byte segments");
+  static constexpr int NSEG = P / 8;
+  static constexpr int BYTES = kChunk * P * 16;
+  __device__ static int row(int r) { return (r >> 3) * (NSEG * 1024) + (r & 7) * 128; }
 };
+__device__ inline int tile_swizzle(int r) { return (r >> 1) & 7; }
 
-// Row order of a 32-token chunk inside the MFMA tiles: operand row m of tile h reads token
-// 16h + perm(m) with perm(4g + s) = 8 (g >> 1) + 2s + (g & 1). A lane's S^T accumulator then
-// holds tokens perm(4g + j) (+16), and the PV transpose reads touch rows two apart, which
-// with the padded row stride keeps both access patterns free of bank conflicts.
-__device__ inline int tile_row(int m) { return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1); }
+// Row order of a 16-token group inside the MFMA tiles: operand row m reads token
+// tile_row(m) = 4 (m & 3) + (m >> 2). A lane's S^T accumulator then holds tokens tile_row(4g + j)
+// (+16), and the four rows of a PV transpose read are 4 apart, which the swizzle spreads over
+// four different 32-byte slot pairs.
+__device__ inline int tile_row(int m) { return 4 * (m & 3) + (m >> 2); }
 
-// Direct global->LDS staging of one 32-token chunk starting at token cbase into `tile`.
-// Lane t < kChunk first resolves token t of the chunk to its byte offset in the unit's pool
-// (-1: padding token, padding slot or past the split end; such rows read zeros, and their
-// scores are masked to -inf so they carry P = 0). Load j (64 lanes) fills tile slots
-// 64j .. 64j+63, which span at most three tile rows: each lane takes its row's offset from the
-// lane that resolved it (scalar lane reads) and adds its 16-byte piece. The calling wave
-// issues loads [j0, j0 + n_loads) of the chunk.
-template <int P, int PP, int LPW_MAX>
-__device__ __forceinline__ void stage_chunk(uint16_t* tile, const int32_t* s_idx,
-                                            const uint8_t* pool_u, int cbase, int tok_end,
-                                            int rec_begin, int tpr_shift, int R, int token_bytes,
-                                            int j0, int n_loads) {
+// Direct global->LDS load of one block, segment SEG of row group rg: `src` is this lane's row (row
+// 8 rg + lane / 8) already advanced by the lane's 16-byte piece. The load's immediate offset
+// moves both addresses.
+template <int P, int SEG>
+__device__ __forceinline__ void stage_block(uint8_t* tile, int rg, const uint8_t* src) {
+  __builtin_amdgcn_global_load_lds(
+      src, (lds_void*)(tile + (rg * Tile<P>::NSEG + SEG) * 1024 - SEG * 128), 16, SEG * 128, 0);
+}
+template <int P>
+__device__ __forceinline__ void stage_rows(uint8_t* tile, int rg, const uint8_t* src) {
+  static_for<Tile<P>::NSEG>([&](auto seg) { stage_block<P, seg>(tile, rg, src); });
+}
+// The 16-byte piece (times 16) that a lane fetches for its row of row group rg.
+__device__ inline int stage_piece(int lane, int rg) {
+  return ((lane & 7) ^ tile_swizzle(8 * rg + (lane >> 3))) << 4;
+}
+
+// Where each lane reads its row of row groups rg0 .. rg0 + N - 1 of the 32-token chunk starting at
+// token cbase. Padding tokens, padding slots and tokens past the split end read zeros (their
+// scores are masked to -inf, so they carry P = 0).
+template <int N>
+__device__ __forceinline__ void chunk_rows(const uint8_t* (&src)[N], const int32_t* s_idx,
+                                           const uint8_t* pool_u, int cbase, int tok_end,
+                                           int rec_begin, int tpr_shift, int R, int token_bytes,
+                                           int rg0) {
   // recompute the per-lane arithmetic here instead of keeping it live across the loop
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
-  const int tk = cbase + lane;
-  const bool in_chunk = lane < kChunk && tk < tok_end;
-  const int32_t s = s_idx[in_chunk ? (tk >> tpr_shift) - rec_begin : 0];
-  const int toff =
-      (in_chunk && s >= 0) ? s * R + (tk & ((1 << tpr_shift) - 1)) * token_bytes : -1;
 #pragma unroll
-  for (int jj = 0; jj < LPW_MAX; ++jj) {
-    if (jj < n_loads) {  // wave-uniform
-      const int j = j0 + jj;
-      const int t0 = (64 * j) / PP;
-      int c = 64 * j - t0 * PP + lane;
-      int o = __builtin_amdgcn_readlane(toff, t0);
-      const int o1 = __builtin_amdgcn_readlane(toff, t0 + 1);
-      if (c >= PP) { c -= PP; o = o1; }
-      if constexpr (PP < 64) {  // a load of 64 slots can reach a third row
-        const int o2 = __builtin_amdgcn_readlane(toff, t0 + 2);
-        if (c >= PP) { c -= PP; o = o2; }
-      }
-      const bool real = o >= 0 && c < P;
-      const uint8_t* src =
-          real ? pool_u + (uint32_t)o + 16 * c : g_zero_token + 16 * (c < P ? c : 0);
-      __builtin_amdgcn_global_load_lds(src, (lds_void*)(tile + 64 * j * 8), 16, 0, 0);
-    }
+  for (int i = 0; i < N; ++i) {
+    const int rg = rg0 + i;
+    const int tk = cbase + 8 * rg + (lane >> 3);
+    const bool in = tk < tok_end;
+    const int32_t s = s_idx[in ? (tk >> tpr_shift) - rec_begin : 0];
+    const uint32_t off = (uint32_t)(s * R + (tk & ((1 << tpr_shift) - 1)) * token_bytes);
+    src[i] = ((in && s >= 0) ? pool_u + off : g_zero_token) + stage_piece(lane, rg);
   }
 }
 
-// The calling wave's loads of the current chunk are done once at most `younger` later chunks'
-// loads (n_loads each) are outstanding; then the workgroup synchronises.
-template <int NST, int LPW_MAX, int LPW_MIN>
-__device__ __forceinline__ void wait_chunk(int younger, bool max_loads) {
-  if constexpr (NST == 2) {
-    wait_loads_and_barrier<0>();
-  } else if (max_loads) {
-    if (younger >= 2) wait_loads_and_barrier<(NST - 2) * LPW_MAX>();
-    else if (younger == 1) wait_loads_and_barrier<LPW_MAX>();
-    else wait_loads_and_barrier<0>();
-  } else {
-    if (younger >= 2) wait_loads_and_barrier<(NST - 2) * LPW_MIN>();
-    else if (younger == 1) wait_loads_and_barrier<LPW_MIN>();
-    else wait_loads_and_barrier<0>();
-  }
+// The calling wave's loads of the current chunk are done once at most `younger` (at most
+// NST - 2) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises.
+template <int NST, int LPW>
+__device__ __forceinline__ void wait_chunk(int younger) {
+  if (NST > 3 && younger >= 2) wait_loads_and_barrier<(NST > 3 ? 2 : 0) * LPW>();
+  else if (NST > 2 && younger >= 1) wait_loads_and_barrier<(NST > 2 ? 1 : 0) * LPW>();
+  else wait_loads_and_barrier<0>();
 }
 
 template <int DQK, int DV, int VOFF, int HW, int TW, int NST>
 __global__ __launch_bounds__(64 * HW * TW, (HW * TW >= 8) ? 2 : 1)
 void attn_partial_kernel(AttnArgs a) {
   constexpr int TE = (DQK > VOFF + DV) ? DQK : VOFF + DV;  // bf16 per token used here
-  constexpr int P = TE / 8;                                 // 16-byte pieces per token
-  constexpr int PP = TileRow<P>::PP;                        // pieces per LDS row
-  constexpr int NL = ((kChunk - 1) * PP + P + 63) / 64;     // 64-lane loads per chunk
-  constexpr int TILE = NL * 64 * 8;                         // bf16 per chunk tile
-  constexpr int LPW_MAX = (NL + HW - 1) / HW;               // loads per wave (first waves)
-  constexpr int LPW_MIN = NL / HW;                          // loads per wave (last waves)
-  constexpr int NL_REM = NL % HW;                           // waves doing LPW_MAX loads
+  using T = Tile<TE / 8>;
+  constexpr int RGW = 4 / HW;              // row groups of a chunk that one head wave stages
+  constexpr int LPW = RGW * T::NSEG;       // its loads per chunk
   constexpr int NKK = DQK / 32;
   constexpr int NOUT = DV / 16;
   static_assert(DQK % 32 == 0 && DV % 16 == 0 && VOFF % 8 == 0, "shape");
-  static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPW_MAX < 64, "pipeline depth");
-  __shared__ __align__(16) uint16_t s_kv[TW * NST * TILE];
+  static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPW < 64, "pipeline depth");
+  __shared__ __align__(1024) uint8_t s_kv[TW * NST * T::BYTES];
   __shared__ int32_t s_idx[kMaxSplitRecords];  // the split's record indices, -1 = skip
   __shared__ uint32_t s_valid[kMaxSplitTokens / 32];  // bit t of word c: token 32c+t attends
 
@@ -281,33 +295,21 @@ void attn_partial_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int hg = wave % HW, tg = wave / HW;
   const int g = lane >> 4;
-  uint16_t* s_tiles = s_kv + tg * NST * TILE;
+  uint8_t* s_tiles = s_kv + tg * NST * T::BYTES;
 
   const int tok_begin = split * a.split_tokens;
   const int tok_end = min(a.n_tok, tok_begin + a.split_tokens);
   const int rec_begin = tok_begin >> a.tpr_shift;
   const int n_rec = ((tok_end - 1) >> a.tpr_shift) - rec_begin + 1;
-  {
-    const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
-    for (int i = tid; i < n_rec; i += 64 * HW * TW) {
-      const int32_t s = idx_u[i];
-      s_idx[i] = (s >= 0 && s < a.rec_per_unit) ? s : -1;
-    }
-  }
+  const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
+  auto checked = [&](int32_t r) { return (r >= 0 && r < a.rec_per_unit) ? r : -1; };
+  const int32_t idx0 = idx_u[min(tid, n_rec - 1)];  // in flight beside the query
   const uint8_t* pool_u = a.pool + (int64_t)unit * a.rec_per_unit * a.R;
 
   const int head = hb * 16 * HW + hg * 16 + (lane & 15);
   const bool head_ok = head < a.H;
-
-  f32x4 o[NOUT];
-#pragma unroll
-  for (int n = 0; n < NOUT; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-
-  __syncthreads();  // s_idx is ready
   // Q^T operand, loaded unconditionally (a head past H reads head 0's row: its scores are never
-  // stored and, being head 0's, move no reference max that head 0 does not) and before the
-  // validity masks are written and the first chunks issued, so that it is in flight meanwhile
+  // stored and, being head 0's, move no reference max that head 0 does not)
   bf16x8_t qreg[NKK];
   {
     const uint16_t* qrow = a.q + ((int64_t)unit * a.H + (head_ok ? head : 0)) * DQK + 8 * g;
@@ -315,6 +317,15 @@ void attn_partial_kernel(AttnArgs a) {
     for (int kk = 0; kk < NKK; ++kk)
       qreg[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(qrow + kk * 32));
   }
+  if (tid < n_rec) s_idx[tid] = checked(idx0);
+  for (int i = tid + 64 * HW * TW; i < n_rec; i += 64 * HW * TW) s_idx[i] = checked(idx_u[i]);
+
+  f32x4 o[NOUT];
+#pragma unroll
+  for (int n = 0; n < NOUT; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+
+  lds_barrier();  // s_idx is ready
   const int n_it = (tok_end - tok_begin + kChunk * TW - 1) / (kChunk * TW);
   {
     // every chunk the token groups iterate over gets its word, including chunks that lie
@@ -331,16 +342,19 @@ void attn_partial_kernel(AttnArgs a) {
     }
   }
 
-  // wave hg stages loads [j0, j0 + n_loads) of each chunk of its token group
-  const int hg_s = __builtin_amdgcn_readfirstlane(hg);
-  const int n_loads = hg_s < NL_REM ? LPW_MAX : LPW_MIN;
-  const int j0 = hg_s * LPW_MIN + min(hg_s, NL_REM);
+  // wave hg stages row groups [hg * RGW, (hg + 1) * RGW) of each chunk of its token group
+  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
   auto issue = [&](int it, int buf) {
-    stage_chunk<P, PP, LPW_MAX>(s_tiles + buf * TILE, s_idx, pool_u,
-                                tok_begin + it * kChunk * TW + tg * kChunk, tok_end, rec_begin,
-                                a.tpr_shift, a.R, a.token_bytes, j0, n_loads);
+    const uint8_t* src[RGW];
+    chunk_rows(src, s_idx, pool_u, tok_begin + it * kChunk * TW + tg * kChunk, tok_end, rec_begin,
+               a.tpr_shift, a.R, a.token_bytes, rg0);
+#pragma unroll
+    for (int i = 0; i < RGW; ++i) stage_rows<TE / 8>(s_tiles + buf * T::BYTES, rg0 + i, src[i]);
   };
-  auto wait = [&](int younger) { wait_chunk<NST, LPW_MAX, LPW_MIN>(younger, hg < NL_REM); };
+  // the query has arrived before the first chunk is issued: a wait for it inside the loop would
+  // drain the chunks in flight
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qreg[kk]));
 
 #pragma unroll
   for (int st = 0; st < NST - 1; ++st)
@@ -354,59 +368,64 @@ void attn_partial_kernel(AttnArgs a) {
   float cmax = -INFINITY;
   int it = 0;
 
-  auto finish_chunk = [&](const uint16_t* tile) {
+  // the head's largest score from its four lanes' largest
+  auto head_max = [](float v) {
+    v = fmaxf(v, __shfl_xor(v, 16, 64));
+    return fmaxf(v, __shfl_xor(v, 32, 64));
+  };
+  auto finish_chunk = [&](const uint8_t* tile) {
     uint32_t pw[4];
-    float psum = 0.f;
-    if (m_run == -INFINITY) {
-      pw[0] = pw[1] = pw[2] = pw[3] = 0u;
-    } else {
 #pragma unroll
-      for (int j = 0; j < 8; j += 2) pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], m_run, &psum);
+    for (int j = 0; j < 8; j += 2)
+      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
+    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
+#pragma unroll
+      for (int j = 0; j < 4; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
     }
-    psum += __shfl_xor(psum, 16, 64);
-    psum += __shfl_xor(psum, 32, 64);
-    l_run += psum;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) l_run = add_weights(pw[j], l_run);
     const bf16x8_t pa = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});
     // V operand by transpose reads: in each 16-lane group, lane 4s+q addresses
-    // V[token][16n + 4q .. +3] of token perm(4g+s) (first read) or 16+perm(4g+s) (second
+    // V[token][16n + 4q .. +3] of token tile_row(4g+s) (first read) or 16 further (second
     // read); lane t then holds V[those tokens][16n + t], i.e. B[k = 8g .. 8g+7][n = t], in the
     // token order of this lane's P values.
-    const int ts = (lane & 15) >> 2, q4 = (lane & 3) * 4;
-    const uint32_t vrow0 = lds_addr(tile + tile_row(4 * g + ts) * PP * 8 + VOFF + q4);
-    const uint32_t vrow1 = vrow0 + 2 * (16 * PP * 8);
+    const int vr = tile_row(4 * g + ((lane & 15) >> 2));  // row; the second read's is 16 further
+    const uint32_t vrow = lds_addr(tile + T::row(vr) + 8 * (lane & 1));
+    const int vp = (((lane & 3) >> 1) ^ tile_swizzle(vr)) << 4;
     // transpose reads VD output tiles ahead of their MFMAs (opaque LDS reads, see lds_read_b128)
     constexpr int VD = 3;
     static_assert(VD == 3 && NOUT > VD, "the waits below count a ring of 3 read pairs");
+    static_assert(VOFF % 64 == 0 && DV % 64 == 0, "V starts on a segment");
     v4i16 vlo[VD], vhi[VD];
-    auto vread = [&](int n, int slot) {
-      vlo[slot] = lds_read_tr16_b64(vrow0 + 2 * 16 * n);
-      vhi[slot] = lds_read_tr16_b64(vrow1 + 2 * 16 * n);
+    uint32_t va[4];  // tiles n, n + 4, ...: dims 16n sit at piece 2n of segment VOFF / 64 + n / 4
+#pragma unroll
+    for (int n = 0; n < 4; ++n) va[n] = vrow + (vp ^ (32 * n));
+    auto vread = [&](auto n) {
+      constexpr int OFF = (VOFF / 64 + n / 4) * 1024;
+      vlo[n % VD] = lds_read_tr16_b64<OFF>(va[n & 3]);
+      vhi[n % VD] = lds_read_tr16_b64<OFF + 2 * T::NSEG * 1024>(va[n & 3]);
     };
-#pragma unroll
-    for (int n = 0; n < VD; ++n) vread(n, n);
-#pragma unroll
-    for (int n = 0; n < NOUT; ++n) {
+    static_for<VD>(vread);
+    static_for<NOUT>([&](auto n) {
       // the reads issued after tile n's pair: those of tiles n+1 .. min(n+VD-1, NOUT-1)
-      const int later = NOUT - 1 - n < VD - 1 ? NOUT - 1 - n : VD - 1;
-      if (later == 2) lgkm_wait2<4>(vlo[n % VD], vhi[n % VD]);
-      else if (later == 1) lgkm_wait2<2>(vlo[n % VD], vhi[n % VD]);
-      else lgkm_wait2<0>(vlo[n % VD], vhi[n % VD]);
+      constexpr int later = NOUT - 1 - n < VD - 1 ? NOUT - 1 - n : VD - 1;
+      lgkm_wait2<2 * later>(vlo[n % VD], vhi[n % VD]);
       const bf16x8_t vb = __builtin_bit_cast(
           bf16x8_t, __builtin_shufflevector(vlo[n % VD], vhi[n % VD], 0, 1, 2, 3, 4, 5, 6, 7));
       o[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb, o[n], 0, 0, 0);
-      if (n + VD < NOUT) vread(n + VD, n % VD);
+      if constexpr (n + VD < NOUT) vread(std::integral_constant<int, n + VD>{});
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
 
   for (;;) {
     for (; it < n_it; ++it) {
       // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
-      wait(min(NST - 2, n_it - 1 - it));
-      const uint16_t* tile = s_tiles + (it % NST) * TILE;
+      wait_chunk<NST, LPW>(min(NST - 2, n_it - 1 - it));
+      const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
       const int cbase = tok_begin + it * kChunk * TW + tg * kChunk;
       // the chunk's validity word, read before the next chunk's loads are issued
-      const uint32_t vmask = s_valid[(cbase - tok_begin) >> 5];
+      const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[(cbase - tok_begin) >> 5]);
       __builtin_amdgcn_sched_barrier(0);
       // every wave is past its reads of buffer (it-1) % NST: refill it with chunk it+NST-1
       if (it + NST - 1 < n_it) issue(it + NST - 1, (it + NST - 1) % NST);
@@ -416,47 +435,53 @@ void attn_partial_kernel(AttnArgs a) {
       // its pair is in
       s0 = f32x4{0.f, 0.f, 0.f, 0.f};
       s1 = f32x4{0.f, 0.f, 0.f, 0.f};
-      const uint32_t k0 = lds_addr(tile + (tile_row(lane & 15) * PP + g) * 8);
-      const uint32_t k1 = k0 + 2 * (16 * PP * 8);
+      const int kr = tile_row(lane & 15);
+      const uint32_t krow = lds_addr(tile + T::row(kr));
+      const int kp = (g ^ tile_swizzle(kr)) << 4;  // piece 4 kk + g: kk odd is 64 bytes apart
+      const uint32_t ka_even = krow + kp, ka_odd = krow + (kp ^ 64);
       static_assert(NKK <= 8, "lgkmcnt holds at most 15 outstanding reads");
       u32x4 ka[NKK], kb[NKK];
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        ka[kk] = lds_read_b128(k0 + 2 * kk * 32);
-        kb[kk] = lds_read_b128(k1 + 2 * kk * 32);
-      }
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        lgkm_wait2_upto<2 * (NKK - 1)>(2 * (NKK - 1 - kk), ka[kk], kb[kk]);
+      static_for<NKK>([&](auto kk) {
+        const uint32_t ad = (kk & 1) ? ka_odd : ka_even;
+        ka[kk] = lds_read_b128<(kk / 2) * 1024>(ad);
+        kb[kk] = lds_read_b128<(kk / 2) * 1024 + 2 * T::NSEG * 1024>(ad);
+      });
+      static_for<NKK>([&](auto kk) {
+        lgkm_wait2<2 * (NKK - 1 - kk)>(ka[kk], kb[kk]);
         s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk]),
                                                     qreg[kk], s0, 0, 0, 0);
         s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kb[kk]),
                                                     qreg[kk], s1, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-      }
-      int gq = g;
-      asm volatile("" : "+v"(gq));
+      });
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int bit = j < 4 ? tile_row(4 * gq + j) : 16 + tile_row(4 * gq + (j - 4));
-        const float raw = j < 4 ? s0[j] : s1[j - 4];
-        sc[j] = ((vmask >> bit) & 1u) ? raw * a.scale_log2 : -INFINITY;
+      for (int j = 0; j < 8; ++j) sc[j] = j < 4 ? s0[j] : s1[j - 4];
+      if (vmask != 0xFFFFFFFFu) {  // uniform: a chunk with padding
+        int gq = g;
+        asm volatile("" : "+v"(gq));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int bit = j < 4 ? tile_row(4 * gq + j) : 16 + tile_row(4 * gq + (j - 4));
+          sc[j] = ((vmask >> bit) & 1u) ? sc[j] : -INFINITY;
+        }
       }
       cmax = sc[0];
 #pragma unroll
       for (int j = 1; j < 8; ++j) cmax = fmaxf(cmax, sc[j]);
-      cmax = fmaxf(cmax, __shfl_xor(cmax, 16, 64));
-      cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
+      cmax *= a.scale_log2;  // this lane's quarter of the head's scores
       // Validity is per token, so every head of the wave agrees on whether m_run is -inf.
       // While it is, O and l are exactly zero and the reference max can simply be set.
-      if (m_run == -INFINITY) m_run = cmax;
-      else if (__ballot(cmax > m_run + kRescaleSlack)) break;
+      if (__ballot(m_run == -INFINITY)) {
+        const float all = head_max(cmax);
+        if (m_run == -INFINITY) m_run = all;
+      }
+      if (__ballot(cmax > m_run + kRescaleSlack)) break;
       finish_chunk(tile);
     }
     if (it >= n_it) break;
     // rare path: move the reference max of the heads whose scores outgrew it
-    const float m_new = fmaxf(m_run, cmax);
-    const float alpha = exp2f(m_run - m_new);
+    const float m_new = fmaxf(m_run, head_max(cmax));
+    const float alpha = m_run == -INFINITY ? 1.f : exp2f(m_run - m_new);  // -inf: l and O are 0
     l_run *= alpha;
     m_run = m_new;
     float al[4];
@@ -467,9 +492,12 @@ void attn_partial_kernel(AttnArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) o[n][j] *= al[j];
     }
-    finish_chunk(s_tiles + (it % NST) * TILE);
+    finish_chunk(s_tiles + (it % NST) * T::BYTES);
     ++it;
   }
+
+  l_run += __shfl_xor(l_run, 16, 64);  // each lane summed its quarter of the head's weights
+  l_run += __shfl_xor(l_run, 32, 64);
 
   // ---- partial results of this (split, token group) ----
   const int part = split * TW + tg;
@@ -508,7 +536,7 @@ constexpr float kMlaSlack = 64.0f;
 __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t* s_idx,
                                                 const uint32_t* s_valid, int unit, int split,
                                                 int tok_begin, int tok_end, int rec_begin,
-                                                int head0) {
+                                                int head0, bool direct) {
   constexpr int DQK = 576, DV = 512;
   const int lane = threadIdx.x & 63;
   const uint8_t* pool_u = a.pool + (int64_t)unit * a.rec_per_unit * a.R;
@@ -544,6 +572,13 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
         acc[e] = acc[e] * alpha + pr * bf16_to_f32(kt[lane * (DV / 64) + e]);
       m = m_new;
     }
+    if (direct) {
+      const float inv = l > 0.f ? 1.f / l : 0.f;
+      float* oh = a.out + ((int64_t)unit * a.H + head) * DV + lane * (DV / 64);
+#pragma unroll
+      for (int e = 0; e < DV / 64; ++e) oh[e] = acc[e] * inv;
+      continue;
+    }
     float* po = a.part_o + ((int64_t)unit * a.n_parts + split) * a.Hp * DV;
 #pragma unroll
     for (int e = 0; e < DV / 64; ++e) po[mla_part_offset(head, lane * (DV / 64) + e)] = acc[e];
@@ -564,25 +599,24 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 //                                                   output tiles, V by LDS transpose reads
 // A lane holds 16 of a head's 32 scores (the other 16 are in lane ^ 32), which are exactly its
 // P operands of the two PV k-steps; O (16 tiles x 16 fp32 per lane) lives in accumulators.
-template <int HW, int TG, int NST, bool PACED>
+template <int HW, int TG, int NST, bool PACED, bool DIRECT>
 __global__ __launch_bounds__(64 * HW * TG, 1)
 void attn_mla_kernel(AttnArgs a) {
   constexpr int DQK = 576, DV = 512;
   constexpr int NW = HW * TG;
-  constexpr int P = DQK / 8;                              // 16-byte pieces per token
-  constexpr int PP = TileRow<P>::PP;                      // pieces per LDS row
-  constexpr int NL = ((kChunk - 1) * PP + P + 63) / 64;   // 64-lane loads per chunk
-  constexpr int TILE = NL * 64 * 8;                       // bf16 per chunk tile
-  constexpr int LPW_MAX = (NL + HW - 1) / HW;             // a group's loads per head wave
-  constexpr int LPW_MIN = NL / HW;
-  constexpr int NL_REM = NL % HW;
+  using T = Tile<DQK / 8>;
+  constexpr int RGW = 4 / HW;                // row groups of a chunk that one head wave stages
+  constexpr int LPW = RGW * T::NSEG;         // its loads per chunk
+  constexpr int QTG = (HW + TG - 1) / TG;    // query tiles (32 heads) per token group
+  constexpr int PRE = NST - QTG;             // chunks issued while the query is in the tiles
   constexpr int NKK = DQK / 16;  // QK k-steps
   constexpr int NDV = DV / 32;   // PV output tiles
-  static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPW_MAX < 64, "pipeline depth");
+  static_assert(NST >= 2 && NST <= 4 && PRE >= 0 && (NST - 2) * LPW < 64 && PRE * LPW < 64,
+                "pipeline depth");
   static_assert(TG == 1 || TG == 2, "token groups");
-  static_assert(TG == 1 || TG * NST * TILE * 2 >= HW * (64 * 64 * 16 + 32 * 8),
+  static_assert(TG == 1 || TG * NST * T::BYTES >= HW * (64 * 64 * 16 + 32 * 8),
                 "the tiles hold one group's results for the merge");
-  __shared__ __align__(16) uint16_t s_kv[TG * NST * TILE];
+  __shared__ __align__(1024) uint8_t s_kv[TG * NST * T::BYTES];
   __shared__ int32_t s_idx[kMaxSplitRecords];         // the split's record indices, -1 = skip
   __shared__ uint32_t s_valid[kMaxSplitTokens / 32];  // bit t of word c: token 32c+t attends
   __shared__ int s_fallback;                           // some score outgrew its reference
@@ -602,39 +636,67 @@ void attn_mla_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int hg = wave % HW, tg = wave / HW;  // head wave within the token group, token group
-  uint16_t* s_tiles = s_kv + tg * NST * TILE;
+  uint8_t* s_tiles = s_kv + tg * NST * T::BYTES;
 
   const int tok_begin = split * a.split_tokens;
   const int tok_end = min(a.n_tok, tok_begin + a.split_tokens);
   const int rec_begin = tok_begin >> a.tpr_shift;
   const int n_rec = ((tok_end - 1) >> a.tpr_shift) - rec_begin + 1;
-  {
-    const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
-    for (int i = tid; i < n_rec; i += 64 * NW) {
-      const int32_t s = idx_u[i];
-      s_idx[i] = (s >= 0 && s < a.rec_per_unit) ? s : -1;
-    }
-  }
+  const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
+  auto checked = [&](int32_t r) { return (r >= 0 && r < a.rec_per_unit) ? r : -1; };
+  const int32_t idx0 = idx_u[min(tid, n_rec - 1)];
   const uint8_t* pool_u = a.pool + (int64_t)unit * a.rec_per_unit * a.R;
 
-  if (tid == 0) s_fallback = 0;
-  __syncthreads();  // s_idx is ready
   const int head0 = hb * 32 * HW + hg * 32;  // first head of this wave
   const int head = head0 + col;
   const bool head_ok = head < a.H;
-  // Q^T operand: Q[head][16kk + 8 half .. +7], loaded unconditionally (a head past H reads head
-  // 0's row: its scores are never stored and, equal to head 0's, change no split-level
-  // decision). Unpaced, its loads go out first: they are in flight while the validity masks
-  // are written and the first chunks issued. Paced, they follow the first chunks' arrival
-  // (below), which spreads the workgroups' start-up traffic.
-  bf16x8_t qreg[NKK];
-  const uint16_t* qrow = a.q + ((int64_t)unit * a.H + (head_ok ? head : 0)) * DQK + 8 * half;
-  auto load_q = [&]() {
+  // The query reaches its registers through LDS: the 32 rows of head wave hg are one tile, staged
+  // like a chunk by the token groups' waves of that head wave, in a chunk buffer that the loop
+  // fills only after they are read (buffer NST - 1 - hg / TG of group hg % TG). Read straight
+  // from memory in operand order, every lane of a load touches a cache line of its own: that
+  // took 3.2 us per workgroup of a 16-unit call. A head past H reads head 0's row: its scores
+  // are never stored and, equal to head 0's, change no split-level decision.
+  uint8_t* q_tile = s_kv + ((hg % TG) * NST + NST - 1 - hg / TG) * T::BYTES;
+  auto stage_q = [&]() {
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
-      qreg[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(qrow + kk * 16));
+    for (int i = 0; i < 4 / TG; ++i) {
+      const int rg = __builtin_amdgcn_readfirstlane(tg) * (4 / TG) + i;
+      const int h = head0 + 8 * rg + (lane >> 3);
+      stage_rows<DQK / 8>(q_tile, rg,
+                          reinterpret_cast<const uint8_t*>(
+                              a.q + ((int64_t)unit * a.H + (h < a.H ? h : 0)) * DQK) +
+                              stage_piece(lane, rg));
+    }
   };
-  if constexpr (!PACED) load_q();
+  bf16x8_t qreg[NKK];
+  auto read_q = [&]() {  // Q[head][16kk + 8 half .. +7]
+    uint32_t qa[4];
+    const int sw = tile_swizzle(col);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      qa[i] = lds_addr(q_tile + T::row(col) + (((2 * i + half) ^ sw) << 4));
+    static_for<NKK / 4>([&](auto j) {  // four reads and their wait in one block
+      u32x4 v0, v1, v2, v3;
+      asm volatile(
+          "ds_read_b128 %0, %4 offset:%8\n\tds_read_b128 %1, %5 offset:%8\n\t"
+          "ds_read_b128 %2, %6 offset:%8\n\tds_read_b128 %3, %7 offset:%8\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3)
+          : "v"(qa[0]), "v"(qa[1]), "v"(qa[2]), "v"(qa[3]), "n"(j * 1024));
+      qreg[4 * j] = __builtin_bit_cast(bf16x8_t, v0);
+      qreg[4 * j + 1] = __builtin_bit_cast(bf16x8_t, v1);
+      qreg[4 * j + 2] = __builtin_bit_cast(bf16x8_t, v2);
+      qreg[4 * j + 3] = __builtin_bit_cast(bf16x8_t, v3);
+    });
+  };
+  // Unpaced, the query goes out behind the indices and is in flight while they are checked and
+  // the first chunks issued. Paced, it follows the first chunks' arrival (below), which spreads
+  // the workgroups' start-up traffic.
+  if constexpr (!PACED) stage_q();
+  if (tid < n_rec) s_idx[tid] = checked(idx0);
+  for (int i = tid + 64 * NW; i < n_rec; i += 64 * NW) s_idx[i] = checked(idx_u[i]);
+  if (tid == 0) s_fallback = 0;
+  lds_barrier();  // s_idx is ready
   // iteration `it` of token group g covers the split's chunk it * TG + g
   const int n_it = (tok_end - tok_begin + kChunk * TG - 1) / (kChunk * TG);
   // every chunk the groups iterate over gets its word, including a last one wholly past the
@@ -650,13 +712,17 @@ void attn_mla_kernel(AttnArgs a) {
     }
   }
 
-  const int w_s = __builtin_amdgcn_readfirstlane(hg);
-  const int n_loads = w_s < NL_REM ? LPW_MAX : LPW_MIN;
-  const int j0 = w_s * LPW_MIN + min(w_s, NL_REM);
+  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
   auto chunk_base = [&](int it) { return tok_begin + (it * TG + tg) * kChunk; };
+  const uint8_t* src[RGW];  // this lane's rows of the chunk to issue next
+  auto rows = [&](int it) {
+    chunk_rows(src, s_idx, pool_u, chunk_base(it), tok_end, rec_begin, a.tpr_shift, a.R,
+               a.token_bytes, rg0);
+  };
   auto issue = [&](int it, int buf) {
-    stage_chunk<P, PP, LPW_MAX>(s_tiles + buf * TILE, s_idx, pool_u, chunk_base(it), tok_end,
-                                rec_begin, a.tpr_shift, a.R, a.token_bytes, j0, n_loads);
+    rows(it);
+#pragma unroll
+    for (int i = 0; i < RGW; ++i) stage_rows<DQK / 8>(s_tiles + buf * T::BYTES, rg0 + i, src[i]);
   };
   f32x16 o[NDV];
 #pragma unroll
@@ -664,52 +730,54 @@ void attn_mla_kernel(AttnArgs a) {
   float m_run = -INFINITY, l_run = 0.f;
   float sc[16];
 
-  auto finish_chunk = [&](const uint16_t* tile) {
+  auto finish_chunk = [&](const uint8_t* tile) {
     uint32_t pw[8];
-    float psum = 0.f;
-    if (m_run == -INFINITY) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pw[j] = 0u;
-    } else {
+    for (int j = 0; j < 16; j += 2)
+      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
+    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
 #pragma unroll
-      for (int j = 0; j < 16; j += 2) pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], m_run, &psum);
+      for (int j = 0; j < 8; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
     }
-    psum += __shfl_xor(psum, 32, 64);
-    l_run += psum;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) l_run = add_weights(pw[j], l_run);
     const bf16x8_t pa0 = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});
     const bf16x8_t pa1 = __builtin_bit_cast(bf16x8_t, u32x4{pw[4], pw[5], pw[6], pw[7]});
     // V operand by transpose reads: in each 16-lane group lane 4s+q addresses row
     // 16kb + 4s + half (+2 for the second read), columns 32n + 16 (col >> 4) + 4q .. +3; lane
     // t of the group then holds V[those rows][32n + 16 (col >> 4) + t], the k order of P.
-    const uint32_t v0 = lds_addr(tile + (4 * ((lane & 15) >> 2) + half) * PP * 8 +
-                                 16 * (col >> 4) + 4 * (lane & 3));
+    const int vr = 4 * ((lane & 15) >> 2) + half;  // row of the first read, k-step 0
+    const int vp = 2 * (col >> 4) + ((lane & 3) >> 1);  // piece of tile 0; tile n: 4 further
+    uint32_t va[2][2];  // [tile parity][first / second read]
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+        va[x][y] = lds_addr(tile + T::row(vr + 2 * y) + 8 * (lane & 1) +
+                            (((vp + 4 * x) ^ tile_swizzle(vr + 2 * y)) << 4));
     // MFMA i = (k-step kb, tile n) = (i / NDV, i % NDV), so consecutive MFMAs update
     // different tiles; its two reads run VD MFMAs ahead
     constexpr int VD = 3;
     constexpr int NM = 2 * NDV;
     static_assert(VD == 3 && NM > VD, "the waits below count a ring of 3 read pairs");
     v4i16 vlo[VD], vhi[VD];
-    auto vread = [&](int i, int slot) {
-      const uint32_t vp = v0 + 2 * ((i / NDV) * 16 * PP * 8 + 32 * (i % NDV));
-      vlo[slot] = lds_read_tr16_b64(vp);
-      vhi[slot] = lds_read_tr16_b64(vp + 2 * (2 * PP * 8));
+    auto vread = [&](auto i) {
+      constexpr int OFF = (i / NDV) * 2 * T::NSEG * 1024 + (i % NDV) / 2 * 1024;
+      vlo[i % VD] = lds_read_tr16_b64<OFF>(va[i & 1][0]);
+      vhi[i % VD] = lds_read_tr16_b64<OFF>(va[i & 1][1]);
     };
-#pragma unroll
-    for (int i = 0; i < VD; ++i) vread(i, i);
-#pragma unroll
-    for (int i = 0; i < NM; ++i) {
+    static_for<VD>(vread);
+    static_for<NM>([&](auto i) {
       // the reads issued after index i's pair: those of indices i+1 .. min(i+VD-1, NM-1)
-      const int later = NM - 1 - i < VD - 1 ? NM - 1 - i : VD - 1;
-      if (later == 2) lgkm_wait2<4>(vlo[i % VD], vhi[i % VD]);
-      else if (later == 1) lgkm_wait2<2>(vlo[i % VD], vhi[i % VD]);
-      else lgkm_wait2<0>(vlo[i % VD], vhi[i % VD]);
+      constexpr int later = NM - 1 - i < VD - 1 ? NM - 1 - i : VD - 1;
+      lgkm_wait2<2 * later>(vlo[i % VD], vhi[i % VD]);
       const bf16x8_t vb = __builtin_bit_cast(
           bf16x8_t, __builtin_shufflevector(vlo[i % VD], vhi[i % VD], 0, 1, 2, 3, 4, 5, 6, 7));
       o[i % NDV] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i < NDV ? pa0 : pa1, vb, o[i % NDV],
                                                            0, 0, 0);
-      if (i + VD < NM) vread(i + VD, i % VD);
+      if constexpr (i + VD < NM) vread(std::integral_constant<int, i + VD>{});
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
 
   // Exponentials are taken against a per-head reference max fixed by the first valid chunk of
@@ -718,23 +786,40 @@ void attn_mla_kernel(AttnArgs a) {
   // an exact fallback after the loop, whose results are then discarded; the loop itself never
   // leaves early, so O has a single update path (the MFMAs) and stays in accumulators.
 #pragma unroll
-  for (int st = 0; st < NST - 1; ++st)
+  for (int st = 0; st < PRE; ++st)
     if (st < n_it) issue(st, st);
   if constexpr (PACED) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    load_q();
+    stage_q();
+    wait_loads_and_barrier<0>();
+  } else if (n_it >= PRE) {
+    wait_loads_and_barrier<PRE * LPW>();
+  } else {
+    wait_loads_and_barrier<0>();
+  }
+  read_q();
+  if constexpr (PRE < NST - 1) {
+    lds_barrier();  // every wave has its query: the other buffers are free for chunks
+#pragma unroll
+    for (int st = PRE; st < NST - 1; ++st)
+      if (st < n_it) issue(st, st);
   }
 
   for (int it = 0; it < n_it; ++it) {
     // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
-    wait_chunk<NST, LPW_MAX, LPW_MIN>(min(NST - 2, n_it - 1 - it), w_s < NL_REM);
-    const uint16_t* tile = s_tiles + (it % NST) * TILE;
+    wait_chunk<NST, LPW>(min(NST - 2, n_it - 1 - it));
+    const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
     const int cbase = chunk_base(it);
     // the chunk's validity word, read before the next chunk's loads are issued
-    const uint32_t vmask = s_valid[(cbase - tok_begin) >> 5];
+    const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[(cbase - tok_begin) >> 5]);
     __builtin_amdgcn_sched_barrier(0);
-    // every wave is past its reads of buffer (it-1) % NST: refill it with chunk it+NST-1
-    if (it + NST - 1 < n_it) issue(it + NST - 1, (it + NST - 1) % NST);
+    // Every wave is past its reads of buffer (it-1) % NST: it takes chunk it+NST-1, whose loads
+    // go out LPI at a time between the score MFMAs. Issued in one run they would hold the wave
+    // back: the CU's address path takes a 64-lane 16-byte load about every 16 cycles, 0.5 us
+    // for a chunk of each token group, with the MFMAs waiting behind it.
+    const bool more = it + NST - 1 < n_it;
+    uint8_t* next = s_tiles + ((it + NST - 1) % NST) * T::BYTES;
+    if (more) rows(it + NST - 1);
 
     // ---- scores: S^T for the chunk's 32 tokens x this wave's 32 heads ----
     // K operand reads run KD k-steps ahead of the MFMAs (a small register ring; the
@@ -743,54 +828,94 @@ void attn_mla_kernel(AttnArgs a) {
     // the accumulation registers. Hazards hidden from the compiler by the assembly are
     // covered in it: wait states before each MFMA for a just-written operand, and after the
     // last one before the scores are read.
+    constexpr int LPI = 3;  // one branch for three loads
+    static_assert(LPW % LPI == 0 && LPW <= NKK, "the chunk's loads fit between the MFMAs");
     constexpr int KD = 4;
-    static_assert(KD == 4 && NKK > KD, "the waits below count a ring of 4 reads");
+    static_assert(KD == 4 && NKK > KD, "a ring of 4 reads, one address register each");
     f32x16 sacc, sacc1;  // even / odd k-steps: two independent MFMA chains
-    const uint32_t krow = lds_addr(tile + (mla_row(col) * PP + half) * 8);
+    const int kr = mla_row(col);
+    uint32_t ka[4];  // piece 2 kk + half of k-steps kk, kk + 4, ...
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      ka[i] = lds_addr(tile + T::row(kr) + (((2 * i + half) ^ tile_swizzle(kr)) << 4));
     u32x4 kbuf[KD];
-#pragma unroll
-    for (int kk = 0; kk < KD; ++kk) kbuf[kk] = lds_read_b128(krow + kk * 32);
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
+    static_for<KD>([&](auto kk) { kbuf[kk] = lds_read_b128<(kk / 4) * 1024>(ka[kk & 3]); });
+    static_for<NKK>([&](auto kk) {
       // the K reads issued after read kk: those of k-steps kk+1 .. min(kk+KD-1, NKK-1)
-      const int later = NKK - 1 - kk < KD - 1 ? NKK - 1 - kk : KD - 1;
-      f32x16& acc = (kk & 1) ? sacc1 : sacc;
-      if (kk < 2) mfma_qk<KD - 1, true>(acc, kbuf[kk % KD], qreg[kk]);
-      else if (later == 3) mfma_qk<3, false>(acc, kbuf[kk % KD], qreg[kk]);
-      else if (later == 2) mfma_qk<2, false>(acc, kbuf[kk % KD], qreg[kk]);
-      else if (later == 1) mfma_qk<1, false>(acc, kbuf[kk % KD], qreg[kk]);
-      else mfma_qk<0, false>(acc, kbuf[kk % KD], qreg[kk]);
-      if (kk + KD < NKK) kbuf[kk % KD] = lds_read_b128(krow + (kk + KD) * 32);
+      constexpr int later = NKK - 1 - kk < KD - 1 ? NKK - 1 - kk : KD - 1;
+      mfma_qk<later, (kk < 2)>((kk & 1) ? sacc1 : sacc, kbuf[kk % KD], qreg[kk]);
+      if constexpr (kk % LPI == 0 && kk < LPW) {
+        if (more)
+          static_for<LPI>([&](auto i) {
+            constexpr int l = kk + i;
+            stage_block<DQK / 8, l % T::NSEG>(next, rg0 + l / T::NSEG, src[l / T::NSEG]);
+          });
+      }
+      if constexpr (kk + KD < NKK)
+        kbuf[kk % KD] = lds_read_b128<((kk + KD) / 4) * 1024>(ka[kk & 3]);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(sacc), "+v"(sacc1));
     sacc += sacc1;
-    int hq = half;
-    asm volatile("" : "+v"(hq));
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int bit = mla_row(8 * (j >> 2) + 4 * hq + (j & 3));
-      sc[j] = ((vmask >> bit) & 1u) ? sacc[j] * a.scale_log2 : -INFINITY;
+    for (int j = 0; j < 16; ++j) sc[j] = sacc[j];
+    if (vmask != 0xFFFFFFFFu) {  // uniform: a chunk with padding
+      int hq = half;
+      asm volatile("" : "+v"(hq));
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int bit = mla_row(8 * (j >> 2) + 4 * hq + (j & 3));
+        sc[j] = ((vmask >> bit) & 1u) ? sc[j] : -INFINITY;
+      }
     }
     float cmax = sc[0];
 #pragma unroll
     for (int j = 1; j < 16; ++j) cmax = fmaxf(cmax, sc[j]);
-    cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
+    cmax *= a.scale_log2;  // this lane's half of the head's scores
     // Validity is per token, so every head of the wave agrees on whether m_run is -inf; while
     // it is, O and l are exactly zero and the reference can simply be set.
-    if (m_run == -INFINITY) m_run = cmax;
-    else if (__ballot(cmax > m_run + kMlaSlack) && lane == 0) s_fallback = 1;
+    if (__ballot(m_run == -INFINITY)) {
+      const float both = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
+      if (m_run == -INFINITY) m_run = both;
+    }
+    if (__ballot(cmax > m_run + kMlaSlack) && lane == 0) s_fallback = 1;
     finish_chunk(tile);
   }
+  l_run += __shfl_xor(l_run, 32, 64);  // each lane summed its half of the head's weights
   wait_loads_and_barrier<0>();  // no staging in flight; s_fallback is final
   if (s_fallback) {
     if (tg == 0)  // the whole split, for this wave's heads
-      mla_split_exact(a, s_idx, s_valid, unit, split, tok_begin, tok_end, rec_begin, head0);
+      mla_split_exact(a, s_idx, s_valid, unit, split, tok_begin, tok_end, rec_begin, head0, DIRECT);
     return;
   }
-  // ---- partial results of this split, in the accumulator layout (see mla_part_offset) ----
+  // ---- partial results of this split, in the accumulator layout (see mla_part_offset), or the
+  // unit's output when the split is all of it: the merge of one part, bit for bit (weight 1,
+  // one reciprocal of the sum), without its 2 KB per head written and read again ----
+  float* oh = DIRECT ? a.out + ((int64_t)unit * a.H + head0 + 4 * half) * DV + col : nullptr;
   float* po = a.part_o + ((int64_t)unit * a.n_parts + split) * a.Hp * DV +
               (int64_t)(head0 >> 5) * 32 * DV + lane * 4;
+  const int n_head = a.H - head0;  // heads of this wave that exist
+  // heads 8q + 4 half .. +3 of tile n (r: their values; inv: 1 / their sums)
+  auto store = [&](int n, int q, const f32x4& r, const float* inv) {
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (8 * q + 4 * half + e < n_head)
+          oh[(int64_t)(8 * q + e) * DV + 32 * n] = (0.f + r[e]) * inv[e];
+    } else {
+      *reinterpret_cast<f32x4*>(po + (n * 4 + q) * 256) = r;
+    }
+  };
+  // Accumulators are read with explicit v_accvgpr_read (arithmetic on them would make the
+  // compiler move all of O into VGPRs and spill); the reads are assembly, so the wait states
+  // after the last MFMA that wrote them are given here (the barrier above already separates
+  // them by far more).
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+  auto acc = [&](int n, int j) {
+    float x;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(o[n][j]));
+    return x;
+  };
   if constexpr (TG == 2) {
     // The two token groups' results merged per head on the way out, through LDS (the tiles
     // are free now): group 1 leaves its accumulators and (reference max, sum) there; group 0
@@ -816,20 +941,18 @@ void attn_mla_kernel(AttnArgs a) {
     const float a1 = other.x == -INFINITY ? 0.f : exp2f(other.x - m_new);
     l_run = l_run * a0 + other.y * a1;
     m_run = m_new;
+    const float l_inv = l_run > 0.f ? 1.f / l_run : 0.f;
     if (head0 < a.H) {
-      // Accumulators are read with explicit v_accvgpr_read (arithmetic on them would make the
-      // compiler move all of O into VGPRs and spill); the reads are assembly, so the wait states
-      // after the last MFMA that wrote them are given here (the barrier above already separates
-      // them by far more).
-      asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
       // accumulator row 4q + e of a lane is head 8q + 4 half + e of the wave's 32
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        float s0[4], s1[4];
+        if (8 * q >= n_head) break;
+        float s0[4], s1[4], inv[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           s0[e] = __shfl(a0, 8 * q + 4 * half + e, 64);
           s1[e] = __shfl(a1, 8 * q + 4 * half + e, 64);
+          inv[e] = __shfl(l_inv, 8 * q + 4 * half + e, 64);
         }
 #pragma unroll
         for (int n = 0; n < NDV; ++n) {
@@ -837,24 +960,27 @@ void attn_mla_kernel(AttnArgs a) {
           f32x4 r;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            float x;
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(o[n][4 * q + e]));
-            r[e] = x * s0[e] + v[e] * s1[e];
+            r[e] = acc(n, 4 * q + e) * s0[e] + v[e] * s1[e];
           }
-          *reinterpret_cast<f32x4*>(po + (n * 4 + q) * 256) = r;
+          store(n, q, r, inv);
         }
       }
     }
-  } else if (head0 < a.H) {
+  } else {
+    const float l_inv = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
-    for (int n = 0; n < NDV; ++n) {
+    for (int q = 0; q < 4; ++q) {
+      if (8 * q >= n_head) break;
+      float inv[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<f32x4*>(po + (n * 4 + q) * 256) =
-            f32x4{o[n][4 * q], o[n][4 * q + 1], o[n][4 * q + 2], o[n][4 * q + 3]};
+      for (int e = 0; e < 4; ++e) inv[e] = __shfl(l_inv, 8 * q + 4 * half + e, 64);
+#pragma unroll
+      for (int n = 0; n < NDV; ++n)
+        store(n, q, f32x4{acc(n, 4 * q), acc(n, 4 * q + 1), acc(n, 4 * q + 2), acc(n, 4 * q + 3)},
+              inv);
     }
   }
-  if (lane < 32 && head_ok)
+  if (!DIRECT && lane < 32 && head_ok)
     a.part_ml[((int64_t)unit * a.n_parts + split) * a.H + head] = make_float2(m_run, l_run);
 }
 
@@ -997,7 +1123,7 @@ __global__ __launch_bounds__(256) void attn_combine_mla_kernel(CombineMlaArgs a)
   const int64_t pstride = (int64_t)a.Hp * DV;
   const float* pb = a.part_o + (int64_t)unit * np * pstride + (int64_t)b * 32 * DV + 4 * f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  int p = sl;
+  int p = b * 32 + h0 < a.H ? sl : np;  // a group of heads past H is neither stored nor read
   for (; p + 3 * NS < np; p += 4 * NS) {
     f32x4 v[4];
 #pragma unroll
@@ -1047,10 +1173,10 @@ void launch_partial(const AttnArgs& args, hipStream_t stream) {
                      dim3(64 * HW * TW), 0, stream, args);
 }
 
-template <int HW, int TG, int NST, bool PACED = false>
+template <int HW, int TG, int NST, bool PACED = false, bool DIRECT = false>
 void launch_mla(const AttnArgs& args, hipStream_t stream) {
   const int nwg_pad = (args.n_wg + 7) & ~7;
-  hipLaunchKernelGGL((attn_mla_kernel<HW, TG, NST, PACED>), dim3(nwg_pad + args.rp.pf_wg),
+  hipLaunchKernelGGL((attn_mla_kernel<HW, TG, NST, PACED, DIRECT>), dim3(nwg_pad + args.rp.pf_wg),
                      dim3(64 * HW * TG), 0, stream, args);
 }
 
@@ -1070,7 +1196,8 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   AttnPlan p{};
   p.n_tok = top_k * attn->tokens_per_record;
   if (is_mla(*attn)) {
-    // 32 heads per wave; above 32 heads, 2 head waves (64 heads) per workgroup. With 16 or more
+    // 32 heads per wave; up to 32 heads, 1 head wave and two token groups; above, 2 head waves (64
+    // heads) per workgroup. With 16 or more
     // workgroup columns (units x head blocks) there are enough of them for two token groups per
     // workgroup: twice the tokens per partial result at the same workgroup count, which halves
     // the split partials (fp32, 2 KB per head) and the merge. Measured alone, attention + merge
@@ -1082,7 +1209,7 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // the fetch's waves.
     if (H <= 32) {
       p.hw = 1;
-      p.tg = 1;
+      p.tg = 2;
     } else {
       p.hw = 2;
       p.tg = (int64_t)units * ((H + 63) / 64) >= 16 ? 2 : 1;
@@ -1114,7 +1241,7 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   // 1.82 and 3.43 ms unpaced against 1.241, 1.371, 1.519, 1.69 and 3.23 ms paced. At 16 columns
   // and below the chain of attention, merge and resolve is the longer one and the unpaced start
   // wins (16 requests: 1.005 against 1.052 ms; 8 requests: 0.711 against 0.724).
-  p.paced = is_mla(*attn) && (attn->flags & HISPARSE_ATTN_BESIDE_FETCH) && p.tg == 2 &&
+  p.paced = is_mla(*attn) && (attn->flags & HISPARSE_ATTN_BESIDE_FETCH) && p.hw == 2 && p.tg == 2 &&
             (int64_t)units * p.hb > 16;
   int splits;
   if (attn->num_splits > 0) {
@@ -1207,11 +1334,18 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   a.n_wg = units * p.n_wg_splits * p.hb;
   a.scale_log2 = attn.scale * 1.4426950408889634f;
 
+  // a unit that is one part needs no merge: the kernel writes the output itself
+  const bool direct = is_mla(attn) && p.tg == 2 && p.n_parts == 1 &&
+                      !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
+  a.out = out;
   if (is_mla(attn)) {
-    if (p.hw == 1) launch_mla<1, 1, 3>(a, stream);
-    else if (p.tg == 2 && p.paced) launch_mla<2, 2, 2, true>(a, stream);
-    else if (p.tg == 2) launch_mla<2, 2, 2>(a, stream);
-    else launch_mla<2, 1, 4>(a, stream);
+    if (p.hw == 1 && direct) launch_mla<1, 2, 2, false, true>(a, stream);
+    else if (p.hw == 1) launch_mla<1, 2, 2>(a, stream);
+    else if (p.tg == 1) launch_mla<2, 1, 4>(a, stream);
+    else if (p.paced && direct) launch_mla<2, 2, 2, true, true>(a, stream);
+    else if (p.paced) launch_mla<2, 2, 2, true>(a, stream);
+    else if (direct) launch_mla<2, 2, 2, false, true>(a, stream);
+    else launch_mla<2, 2, 2>(a, stream);
   } else {
     switch (p.hw) {
       case 1: launch_partial<128, 128, 128, 1, 4, 2>(a, stream); break;
@@ -1221,7 +1355,7 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (attn.flags & HISPARSE_ATTN_DEFER_MERGE) return hipSuccess;
+  if (direct || (attn.flags & HISPARSE_ATTN_DEFER_MERGE)) return hipSuccess;
   return launch_merge(p, attn, units, out, workspace, stream);
 }
 
