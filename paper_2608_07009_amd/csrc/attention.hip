@@ -72,11 +72,23 @@ struct AttnArgs {
   int32_t split_tokens, n_wg_splits, hb, n_parts, n_wg;
   int32_t Hp;         // latent attention: heads rounded up to 32 (partial-output block layout)
   int32_t idx_units;  // unit u reads index row u % idx_units
+  FastDiv div_hb, div_splits, div_idx;  // by hb, n_wg_splits, idx_units
   float scale_log2;
   // A prefetch replay carried by the launch: extra workgroups after the attention workgroups
   // copy that plan's records (pf_wg = 0: none).
   CarriedReplay rp;
 };
+
+// The arguments an attention workgroup needs before its first memory access, loaded together at
+// the start: left to themselves the scalar loads go out one use at a time, each a round trip.
+__device__ __forceinline__ void load_args(const AttnArgs& a) {
+  asm volatile("" ::"s"(a.pool), "s"(a.q), "s"(a.idx), "s"(a.rec_per_unit), "s"(a.R),
+               "s"(a.token_bytes), "s"(a.tpr_shift), "s"(a.k), "s"(a.H), "s"(a.n_tok));
+  asm volatile("" ::"s"(a.split_tokens), "s"(a.n_wg_splits), "s"(a.hb), "s"(a.n_wg),
+               "s"(a.idx_units), "s"(a.div_hb.magic), "s"(a.div_hb.shift),
+               "s"(a.div_splits.magic), "s"(a.div_splits.shift), "s"(a.div_idx.magic),
+               "s"(a.div_idx.shift), "s"(a.scale_log2));
+}
 
 // Extra workgroup e of a launch: its share of the carried replay. It shares no memory with the
 // launch's own workgroups (other layers' caches), so it needs no synchronisation.
@@ -232,25 +244,91 @@ __device__ inline int stage_piece(int lane, int rg) {
   return ((lane & 7) ^ tile_swizzle(8 * rg + (lane >> 3))) << 4;
 }
 
+// The records of a split: where its tokens' indices are and how a token finds its bytes.
+struct SplitRows {
+  const int32_t* idx;     // the split's record indices in memory
+  const uint8_t* pool;    // the unit's part of the pool
+  int tok_end, rec_begin, tpr_shift, R, token_bytes;
+  int64_t rec_per_unit;
+  __device__ int32_t checked(int32_t r) const { return (r >= 0 && r < rec_per_unit) ? r : -1; }
+  // index entry of token tk (entry 0 for a token past the split end)
+  __device__ int entry(int tk) const { return tk < tok_end ? (tk >> tpr_shift) - rec_begin : 0; }
+  // Token tk of record s. Padding slots (s < 0) and tokens past the split end read zeros: their
+  // scores are masked to -inf, so they carry P = 0.
+  __device__ const uint8_t* row(int tk, int32_t s) const {
+    const uint32_t off = (uint32_t)(s * R + (tk & ((1 << tpr_shift) - 1)) * token_bytes);
+    return (tk < tok_end && s >= 0) ? pool + off : g_zero_token;
+  }
+};
+
 // Where each lane reads its row of row groups rg0 .. rg0 + N - 1 of the 32-token chunk starting at
-// token cbase. Padding tokens, padding slots and tokens past the split end read zeros (their
-// scores are masked to -inf, so they carry P = 0).
+// token cbase, by the checked indices in LDS.
 template <int N>
 __device__ __forceinline__ void chunk_rows(const uint8_t* (&src)[N], const int32_t* s_idx,
-                                           const uint8_t* pool_u, int cbase, int tok_end,
-                                           int rec_begin, int tpr_shift, int R, int token_bytes,
-                                           int rg0) {
+                                           const SplitRows& r, int cbase, int rg0) {
   // recompute the per-lane arithmetic here instead of keeping it live across the loop
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    const int rg = rg0 + i;
-    const int tk = cbase + 8 * rg + (lane >> 3);
-    const bool in = tk < tok_end;
-    const int32_t s = s_idx[in ? (tk >> tpr_shift) - rec_begin : 0];
-    const uint32_t off = (uint32_t)(s * R + (tk & ((1 << tpr_shift) - 1)) * token_bytes);
-    src[i] = ((in && s >= 0) ? pool_u + off : g_zero_token) + stage_piece(lane, rg);
+    const int tk = cbase + 8 * (rg0 + i) + (lane >> 3);
+    src[i] = r.row(tk, s_idx[r.entry(tk)]) + stage_piece(lane, rg0 + i);
+  }
+}
+// The same for a workgroup's first chunk, in two halves: its index entries straight from memory
+// (the first loads of the kernel), and the rows once they are here. The chunk then leaves
+// without waiting for the indices' way through LDS and a barrier.
+template <int N>
+__device__ __forceinline__ void first_entries(int32_t (&e)[N], const SplitRows& r, int cbase,
+                                              int rg0) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    e[i] = r.idx[r.entry(cbase + 8 * (rg0 + i) + (int)((threadIdx.x & 63) >> 3))];
+}
+template <int N>
+__device__ __forceinline__ void first_rows(const uint8_t* (&src)[N], const int32_t (&e)[N],
+                                           const SplitRows& r, int cbase, int rg0) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    src[i] = r.row(cbase + 8 * (rg0 + i) + (lane >> 3), r.checked(e[i])) +
+             stage_piece(lane, rg0 + i);
+}
+
+// The split's n_rec index entries on their way to LDS, NT threads: all loads first, the checked
+// entries stored later.
+template <int NT>
+struct IndexCopy {
+  static constexpr int N = kMaxSplitRecords / NT;
+  int32_t v[N];
+  __device__ __forceinline__ void load(const SplitRows& r, int n_rec) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (u * NT < n_rec) v[u] = r.idx[min((int)threadIdx.x + u * NT, n_rec - 1)];  // uniform
+  }
+  __device__ __forceinline__ void store(int32_t* s_idx, const SplitRows& r, int n_rec) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = threadIdx.x + u * NT;
+      if (u * NT < n_rec && i < n_rec) s_idx[i] = r.checked(v[u]);
+    }
+  }
+};
+
+// Validity words of tokens [tok_begin, tok_begin + span), span a multiple of 32, one 64-token
+// group per wave and step: bit t of word c is token tok_begin + 32 c + t. Tokens past the split
+// end have zero bits.
+template <int NW>
+__device__ __forceinline__ void valid_words(uint32_t* s_valid, const int32_t* s_idx,
+                                            const SplitRows& r, int tok_begin, int span) {
+  const int lane = threadIdx.x & 63;
+  for (int base = (threadIdx.x >> 6) * 64; base < span; base += 64 * NW) {
+    const int tk = tok_begin + base + lane;
+    const uint64_t m = __ballot(tk < r.tok_end && s_idx[r.entry(tk)] >= 0);
+    if (lane == 0) {
+      s_valid[base >> 5] = (uint32_t)m;
+      if (base + 32 < span) s_valid[(base >> 5) + 1] = (uint32_t)(m >> 32);
+    }
   }
 }
 
@@ -278,6 +356,7 @@ void attn_partial_kernel(AttnArgs a) {
   __shared__ int32_t s_idx[kMaxSplitRecords];  // the split's record indices, -1 = skip
   __shared__ uint32_t s_valid[kMaxSplitTokens / 32];  // bit t of word c: token 32c+t attends
 
+  load_args(a);
   // XCD-aware mapping: consecutive workgroup ids go round-robin over the 8 XCDs, so give each
   // XCD a contiguous range of work items; the head blocks of one (unit, split) then share the
   // staged records through the same L2.
@@ -288,9 +367,10 @@ void attn_partial_kernel(AttnArgs a) {
   }
   const int w = (int)(blockIdx.x & 7) * (nwg_pad >> 3) + (int)(blockIdx.x >> 3);
   if (w >= a.n_wg) return;
-  const int hb = w % a.hb;
-  const int split = (w / a.hb) % a.n_wg_splits;
-  const int unit = w / (a.hb * a.n_wg_splits);
+  const int col_split = (int)fastdiv(w, a.div_hb), hb = w - col_split * a.hb;
+  const int unit = (int)fastdiv(col_split, a.div_splits);
+  const int split = col_split - unit * a.n_wg_splits;
+  const int idx_row = unit - (int)fastdiv(unit, a.div_idx) * a.idx_units;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int hg = wave % HW, tg = wave / HW;
@@ -301,10 +381,16 @@ void attn_partial_kernel(AttnArgs a) {
   const int tok_end = min(a.n_tok, tok_begin + a.split_tokens);
   const int rec_begin = tok_begin >> a.tpr_shift;
   const int n_rec = ((tok_end - 1) >> a.tpr_shift) - rec_begin + 1;
-  const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
-  auto checked = [&](int32_t r) { return (r >= 0 && r < a.rec_per_unit) ? r : -1; };
-  const int32_t idx0 = idx_u[min(tid, n_rec - 1)];  // in flight beside the query
-  const uint8_t* pool_u = a.pool + (int64_t)unit * a.rec_per_unit * a.R;
+  const SplitRows rows{a.idx + (int64_t)idx_row * a.k + rec_begin,
+                       a.pool + (int64_t)unit * a.rec_per_unit * a.R,
+                       tok_end, rec_begin, a.tpr_shift, a.R, a.token_bytes, a.rec_per_unit};
+  // wave hg stages row groups [hg * RGW, (hg + 1) * RGW) of each chunk of its token group
+  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
+  const int chunk0 = tok_begin + __builtin_amdgcn_readfirstlane(tg) * kChunk;
+  int32_t entry0[RGW];
+  first_entries(entry0, rows, chunk0, rg0);
+  IndexCopy<64 * HW * TW> ic;
+  ic.load(rows, n_rec);
 
   const int head = hb * 16 * HW + hg * 16 + (lane & 15);
   const bool head_ok = head < a.H;
@@ -317,48 +403,37 @@ void attn_partial_kernel(AttnArgs a) {
     for (int kk = 0; kk < NKK; ++kk)
       qreg[kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(qrow + kk * 32));
   }
-  if (tid < n_rec) s_idx[tid] = checked(idx0);
-  for (int i = tid + 64 * HW * TW; i < n_rec; i += 64 * HW * TW) s_idx[i] = checked(idx_u[i]);
+  const uint8_t* src[RGW];
+  first_rows(src, entry0, rows, chunk0, rg0);
+  // the query has arrived before the first chunk is issued: a wait for it inside the loop would
+  // drain the chunks in flight
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qreg[kk]));
+  auto issue = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < RGW; ++i) stage_rows<TE / 8>(s_tiles + buf * T::BYTES, rg0 + i, src[i]);
+  };
+  auto next_rows = [&](int it) {
+    chunk_rows(src, s_idx, rows, chunk0 + it * kChunk * TW, rg0);
+  };
+  issue(0);
+  ic.store(s_idx, rows, n_rec);
 
   f32x4 o[NOUT];
 #pragma unroll
   for (int n = 0; n < NOUT; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
-
-  lds_barrier();  // s_idx is ready
   const int n_it = (tok_end - tok_begin + kChunk * TW - 1) / (kChunk * TW);
-  {
-    // every chunk the token groups iterate over gets its word, including chunks that lie
-    // wholly past the split end (all zero)
-    const int span = n_it * kChunk * TW;
-    for (int base = wave * 64; base < span; base += 64 * HW * TW) {
-      const int tk = tok_begin + base + lane;
-      const bool ok = tk < tok_end && s_idx[(tk >> a.tpr_shift) - rec_begin] >= 0;
-      const uint64_t m = __ballot(ok);
-      if (lane == 0) {
-        s_valid[base >> 5] = (uint32_t)m;
-        if (base + 32 < span) s_valid[(base >> 5) + 1] = (uint32_t)(m >> 32);
-      }
+  lds_barrier();  // s_idx is ready
+  // every chunk the token groups iterate over gets its word, including chunks that lie wholly
+  // past the split end
+  valid_words<HW * TW>(s_valid, s_idx, rows, tok_begin, n_it * kChunk * TW);
+#pragma unroll
+  for (int st = 1; st < NST - 1; ++st)
+    if (st < n_it) {
+      next_rows(st);
+      issue(st);
     }
-  }
-
-  // wave hg stages row groups [hg * RGW, (hg + 1) * RGW) of each chunk of its token group
-  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
-  auto issue = [&](int it, int buf) {
-    const uint8_t* src[RGW];
-    chunk_rows(src, s_idx, pool_u, tok_begin + it * kChunk * TW + tg * kChunk, tok_end, rec_begin,
-               a.tpr_shift, a.R, a.token_bytes, rg0);
-#pragma unroll
-    for (int i = 0; i < RGW; ++i) stage_rows<TE / 8>(s_tiles + buf * T::BYTES, rg0 + i, src[i]);
-  };
-  // the query has arrived before the first chunk is issued: a wait for it inside the loop would
-  // drain the chunks in flight
-#pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qreg[kk]));
-
-#pragma unroll
-  for (int st = 0; st < NST - 1; ++st)
-    if (st < n_it) issue(st, st);
 
   // Per chunk: scores (QK), softmax against the running reference max, then P.V. O is touched
   // only by MFMAs inside the loop; the rare move of a head's reference max (growth beyond the
@@ -423,12 +498,14 @@ void attn_partial_kernel(AttnArgs a) {
       // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
       wait_chunk<NST, LPW>(min(NST - 2, n_it - 1 - it));
       const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
-      const int cbase = tok_begin + it * kChunk * TW + tg * kChunk;
       // the chunk's validity word, read before the next chunk's loads are issued
-      const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[(cbase - tok_begin) >> 5]);
+      const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TW + tg]);
       __builtin_amdgcn_sched_barrier(0);
       // every wave is past its reads of buffer (it-1) % NST: refill it with chunk it+NST-1
-      if (it + NST - 1 < n_it) issue(it + NST - 1, (it + NST - 1) % NST);
+      if (it + NST - 1 < n_it) {
+        next_rows(it + NST - 1);
+        issue((it + NST - 1) % NST);
+      }
 
       // ---- scores: S^T tiles for tokens [0,16) and [16,32) of the chunk ----
       // all K reads first (opaque LDS reads, see lds_read_b128), then each k-step's MFMAs once
@@ -599,28 +676,26 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 //                                                   output tiles, V by LDS transpose reads
 // A lane holds 16 of a head's 32 scores (the other 16 are in lane ^ 32), which are exactly its
 // P operands of the two PV k-steps; O (16 tiles x 16 fp32 per lane) lives in accumulators.
-template <int HW, int TG, int NST, bool PACED, bool DIRECT>
-__global__ __launch_bounds__(64 * HW * TG, 1)
+template <int HW, bool PACED, bool DIRECT>
+__global__ __launch_bounds__(128 * HW, 1)
 void attn_mla_kernel(AttnArgs a) {
   constexpr int DQK = 576, DV = 512;
-  constexpr int NW = HW * TG;
+  constexpr int TG = 2, NST = 2, NW = HW * TG;
   using T = Tile<DQK / 8>;
+  static_assert(HW == 1 || HW == 2, "one query tile per token group at most");
   constexpr int RGW = 4 / HW;                // row groups of a chunk that one head wave stages
   constexpr int LPW = RGW * T::NSEG;         // its loads per chunk
-  constexpr int QTG = (HW + TG - 1) / TG;    // query tiles (32 heads) per token group
-  constexpr int PRE = NST - QTG;             // chunks issued while the query is in the tiles
   constexpr int NKK = DQK / 16;  // QK k-steps
   constexpr int NDV = DV / 32;   // PV output tiles
-  static_assert(NST >= 2 && NST <= 4 && PRE >= 0 && (NST - 2) * LPW < 64 && PRE * LPW < 64,
-                "pipeline depth");
-  static_assert(TG == 1 || TG == 2, "token groups");
-  static_assert(TG == 1 || TG * NST * T::BYTES >= HW * (64 * 64 * 16 + 32 * 8),
-                "the tiles hold one group's results for the merge");
+  static_assert(LPW < 64, "the wait counter's range");
+  static_assert(TG * NST * T::BYTES >= NW * (NDV / 2 * 4 * 64 * 16 + 32 * 8 + 96 * 4),
+                "the tiles hold half of each wave's results for the merge");
   __shared__ __align__(1024) uint8_t s_kv[TG * NST * T::BYTES];
   __shared__ int32_t s_idx[kMaxSplitRecords];         // the split's record indices, -1 = skip
   __shared__ uint32_t s_valid[kMaxSplitTokens / 32];  // bit t of word c: token 32c+t attends
   __shared__ int s_fallback;                           // some score outgrew its reference
 
+  load_args(a);
   // XCD-aware mapping, as in attn_partial_kernel
   const int nwg_pad = (a.n_wg + 7) & ~7;
   if ((int)blockIdx.x >= nwg_pad) {  // wave-uniform: the whole workgroup replays
@@ -629,9 +704,10 @@ void attn_mla_kernel(AttnArgs a) {
   }
   const int w = (int)(blockIdx.x & 7) * (nwg_pad >> 3) + (int)(blockIdx.x >> 3);
   if (w >= a.n_wg) return;
-  const int hb = w % a.hb;
-  const int split = (w / a.hb) % a.n_wg_splits;
-  const int unit = w / (a.hb * a.n_wg_splits);
+  const int col_split = (int)fastdiv(w, a.div_hb), hb = w - col_split * a.hb;
+  const int unit = (int)fastdiv(col_split, a.div_splits);
+  const int split = col_split - unit * a.n_wg_splits;
+  const int idx_row = unit - (int)fastdiv(unit, a.div_idx) * a.idx_units;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
@@ -642,21 +718,27 @@ void attn_mla_kernel(AttnArgs a) {
   const int tok_end = min(a.n_tok, tok_begin + a.split_tokens);
   const int rec_begin = tok_begin >> a.tpr_shift;
   const int n_rec = ((tok_end - 1) >> a.tpr_shift) - rec_begin + 1;
-  const int32_t* idx_u = a.idx + (int64_t)(unit % a.idx_units) * a.k + rec_begin;
-  auto checked = [&](int32_t r) { return (r >= 0 && r < a.rec_per_unit) ? r : -1; };
-  const int32_t idx0 = idx_u[min(tid, n_rec - 1)];
-  const uint8_t* pool_u = a.pool + (int64_t)unit * a.rec_per_unit * a.R;
+  const SplitRows rows{a.idx + (int64_t)idx_row * a.k + rec_begin,
+                       a.pool + (int64_t)unit * a.rec_per_unit * a.R,
+                       tok_end, rec_begin, a.tpr_shift, a.R, a.token_bytes, a.rec_per_unit};
+  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
+  // iteration `it` of token group g covers the split's chunk it * TG + g
+  const int chunk0 = tok_begin + __builtin_amdgcn_readfirstlane(tg) * kChunk;
+  int32_t entry0[RGW];
+  first_entries(entry0, rows, chunk0, rg0);
+  IndexCopy<64 * NW> ic;
+  ic.load(rows, n_rec);
 
   const int head0 = hb * 32 * HW + hg * 32;  // first head of this wave
   const int head = head0 + col;
   const bool head_ok = head < a.H;
   // The query reaches its registers through LDS: the 32 rows of head wave hg are one tile, staged
-  // like a chunk by the token groups' waves of that head wave, in a chunk buffer that the loop
-  // fills only after they are read (buffer NST - 1 - hg / TG of group hg % TG). Read straight
+  // like a chunk by both token groups' waves of that head wave, in the second chunk buffer of
+  // group hg, which the loop fills only after they are read. Read straight
   // from memory in operand order, every lane of a load touches a cache line of its own: that
   // took 3.2 us per workgroup of a 16-unit call. A head past H reads head 0's row: its scores
   // are never stored and, equal to head 0's, change no split-level decision.
-  uint8_t* q_tile = s_kv + ((hg % TG) * NST + NST - 1 - hg / TG) * T::BYTES;
+  uint8_t* q_tile = s_kv + (hg * NST + 1) * T::BYTES;
   auto stage_q = [&]() {
 #pragma unroll
     for (int i = 0; i < 4 / TG; ++i) {
@@ -689,46 +771,29 @@ void attn_mla_kernel(AttnArgs a) {
       qreg[4 * j + 3] = __builtin_bit_cast(bf16x8_t, v3);
     });
   };
-  // Unpaced, the query goes out behind the indices and is in flight while they are checked and
-  // the first chunks issued. Paced, it follows the first chunks' arrival (below), which spreads
-  // the workgroups' start-up traffic.
+  // Unpaced, the query goes out behind the index loads and is in flight while they are checked
+  // and the first chunk issued. Paced, it follows the first chunk's arrival (below), which
+  // spreads the workgroups' start-up traffic.
   if constexpr (!PACED) stage_q();
-  if (tid < n_rec) s_idx[tid] = checked(idx0);
-  for (int i = tid + 64 * NW; i < n_rec; i += 64 * NW) s_idx[i] = checked(idx_u[i]);
-  if (tid == 0) s_fallback = 0;
-  lds_barrier();  // s_idx is ready
-  // iteration `it` of token group g covers the split's chunk it * TG + g
-  const int n_it = (tok_end - tok_begin + kChunk * TG - 1) / (kChunk * TG);
-  // every chunk the groups iterate over gets its word, including a last one wholly past the
-  // split end (all zero)
-  const int span = n_it * TG * kChunk;
-  for (int base = wave * 64; base < span; base += 64 * NW) {
-    const int tk = tok_begin + base + lane;
-    const bool ok = tk < tok_end && s_idx[(tk >> a.tpr_shift) - rec_begin] >= 0;
-    const uint64_t m = __ballot(ok);
-    if (lane == 0) {
-      s_valid[base >> 5] = (uint32_t)m;
-      if (base + 32 < span) s_valid[(base >> 5) + 1] = (uint32_t)(m >> 32);
-    }
-  }
-
-  const int rg0 = __builtin_amdgcn_readfirstlane(hg) * RGW;
-  auto chunk_base = [&](int it) { return tok_begin + (it * TG + tg) * kChunk; };
   const uint8_t* src[RGW];  // this lane's rows of the chunk to issue next
-  auto rows = [&](int it) {
-    chunk_rows(src, s_idx, pool_u, chunk_base(it), tok_end, rec_begin, a.tpr_shift, a.R,
-               a.token_bytes, rg0);
-  };
-  auto issue = [&](int it, int buf) {
-    rows(it);
+  first_rows(src, entry0, rows, chunk0, rg0);
 #pragma unroll
-    for (int i = 0; i < RGW; ++i) stage_rows<DQK / 8>(s_tiles + buf * T::BYTES, rg0 + i, src[i]);
-  };
+  for (int i = 0; i < RGW; ++i) stage_rows<DQK / 8>(s_tiles, rg0 + i, src[i]);
+  ic.store(s_idx, rows, n_rec);
+  if (tid == 0) s_fallback = 0;
   f32x16 o[NDV];
 #pragma unroll
-  for (int n = 0; n < NDV; ++n) o[n] = f32x16{};
+  for (int n = 0; n < NDV; ++n) {
+    o[n] = f32x16{};
+    asm volatile("" : "+a"(o[n]));  // cleared here, while the loads are in flight
+  }
   float m_run = -INFINITY, l_run = 0.f;
   float sc[16];
+  const int n_it = (tok_end - tok_begin + kChunk * TG - 1) / (kChunk * TG);
+  lds_barrier();  // s_idx is ready
+  // every chunk the groups iterate over gets its word, including a last one wholly past the
+  // split end
+  valid_words<NW>(s_valid, s_idx, rows, tok_begin, n_it * TG * kChunk);
 
   auto finish_chunk = [&](const uint8_t* tile) {
     uint32_t pw[8];
@@ -748,13 +813,19 @@ void attn_mla_kernel(AttnArgs a) {
     // t of the group then holds V[those rows][32n + 16 (col >> 4) + t], the k order of P.
     const int vr = 4 * ((lane & 15) >> 2) + half;  // row of the first read, k-step 0
     const int vp = 2 * (col >> 4) + ((lane & 3) >> 1);  // piece of tile 0; tile n: 4 further
-    uint32_t va[2][2];  // [tile parity][first / second read]
+    // Accumulator tile n holds dims 32n .. of token group 0's output and dims 32 ((n + 8) % 16) ..
+    // of group 1's, so that at the end each group finishes its tiles 0-7 and leaves the other
+    // group tiles 8-15 with the same code (registers cannot be chosen at run time).
+    uint32_t va[2][2][2];  // [tile half][tile parity][first / second read]
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 2; ++y)
-        va[x][y] = lds_addr(tile + T::row(vr + 2 * y) + 8 * (lane & 1) +
-                            (((vp + 4 * x) ^ tile_swizzle(vr + 2 * y)) << 4));
+      for (int y = 0; y < 2; ++y) {
+        const uint32_t v = lds_addr(tile + T::row(vr + 2 * y) + 8 * (lane & 1) +
+                                    (((vp + 4 * x) ^ tile_swizzle(vr + 2 * y)) << 4));
+        va[0][x][y] = v + 4096 * tg;
+        va[1][x][y] = v - 4096 * tg;
+      }
     // MFMA i = (k-step kb, tile n) = (i / NDV, i % NDV), so consecutive MFMAs update
     // different tiles; its two reads run VD MFMAs ahead
     constexpr int VD = 3;
@@ -763,8 +834,9 @@ void attn_mla_kernel(AttnArgs a) {
     v4i16 vlo[VD], vhi[VD];
     auto vread = [&](auto i) {
       constexpr int OFF = (i / NDV) * 2 * T::NSEG * 1024 + (i % NDV) / 2 * 1024;
-      vlo[i % VD] = lds_read_tr16_b64<OFF>(va[i & 1][0]);
-      vhi[i % VD] = lds_read_tr16_b64<OFF>(va[i & 1][1]);
+      constexpr int h = (i % NDV) / (NDV / 2);
+      vlo[i % VD] = lds_read_tr16_b64<OFF>(va[h][i & 1][0]);
+      vhi[i % VD] = lds_read_tr16_b64<OFF>(va[h][i & 1][1]);
     };
     static_for<VD>(vread);
     static_for<NM>([&](auto i) {
@@ -785,33 +857,20 @@ void attn_mla_kernel(AttnArgs a) {
   // same reference). Scores more than kMlaSlack powers of two above it send the whole split to
   // an exact fallback after the loop, whose results are then discarded; the loop itself never
   // leaves early, so O has a single update path (the MFMAs) and stays in accumulators.
-#pragma unroll
-  for (int st = 0; st < PRE; ++st)
-    if (st < n_it) issue(st, st);
   if constexpr (PACED) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     stage_q();
     wait_loads_and_barrier<0>();
-  } else if (n_it >= PRE) {
-    wait_loads_and_barrier<PRE * LPW>();
   } else {
-    wait_loads_and_barrier<0>();
+    wait_loads_and_barrier<LPW>();
   }
   read_q();
-  if constexpr (PRE < NST - 1) {
-    lds_barrier();  // every wave has its query: the other buffers are free for chunks
-#pragma unroll
-    for (int st = PRE; st < NST - 1; ++st)
-      if (st < n_it) issue(st, st);
-  }
 
   for (int it = 0; it < n_it; ++it) {
-    // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
-    wait_chunk<NST, LPW>(min(NST - 2, n_it - 1 - it));
+    wait_loads_and_barrier<0>();
     const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
-    const int cbase = chunk_base(it);
     // the chunk's validity word, read before the next chunk's loads are issued
-    const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[(cbase - tok_begin) >> 5]);
+    const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TG + tg]);
     __builtin_amdgcn_sched_barrier(0);
     // Every wave is past its reads of buffer (it-1) % NST: it takes chunk it+NST-1, whose loads
     // go out LPI at a time between the score MFMAs. Issued in one run they would hold the wave
@@ -819,7 +878,7 @@ void attn_mla_kernel(AttnArgs a) {
     // for a chunk of each token group, with the MFMAs waiting behind it.
     const bool more = it + NST - 1 < n_it;
     uint8_t* next = s_tiles + ((it + NST - 1) % NST) * T::BYTES;
-    if (more) rows(it + NST - 1);
+    if (more) chunk_rows(src, s_idx, rows, chunk0 + (it + NST - 1) * kChunk * TG, rg0);
 
     // ---- scores: S^T for the chunk's 32 tokens x this wave's 32 heads ----
     // K operand reads run KD k-steps ahead of the MFMAs (a small register ring; the
@@ -891,12 +950,14 @@ void attn_mla_kernel(AttnArgs a) {
   // ---- partial results of this split, in the accumulator layout (see mla_part_offset), or the
   // unit's output when the split is all of it: the merge of one part, bit for bit (weight 1,
   // one reciprocal of the sum), without its 2 KB per head written and read again ----
-  float* oh = DIRECT ? a.out + ((int64_t)unit * a.H + head0 + 4 * half) * DV + col : nullptr;
+  constexpr int HT = NDV / 2;  // output tiles that each group finishes: dims 32 (HT tg + n) ..
+  float* oh = DIRECT ? a.out + ((int64_t)unit * a.H + head0 + 4 * half) * DV + 32 * HT * tg + col
+                     : nullptr;
   float* po = a.part_o + ((int64_t)unit * a.n_parts + split) * a.Hp * DV +
-              (int64_t)(head0 >> 5) * 32 * DV + lane * 4;
+              (int64_t)(head0 >> 5) * 32 * DV + HT * tg * 1024 + lane * 4;
   const int n_head = a.H - head0;  // heads of this wave that exist
   // heads 8q + 4 half .. +3 of tile n (r: their values; inv: 1 / their sums)
-  auto store = [&](int n, int q, const f32x4& r, const float* inv) {
+  auto store = [&](int n, int q, const f32x4& r, const f32x4& inv) {
     if constexpr (DIRECT) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -916,72 +977,55 @@ void attn_mla_kernel(AttnArgs a) {
     asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(o[n][j]));
     return x;
   };
-  if constexpr (TG == 2) {
-    // The two token groups' results merged per head on the way out, through LDS (the tiles
-    // are free now): group 1 leaves its accumulators and (reference max, sum) there; group 0
-    // rescales both to the larger reference and adds, in that fixed order, into the stores.
-    f32x4* s_o = reinterpret_cast<f32x4*>(s_kv) + hg * 64 * 64;  // [64 regs / 4][64 lanes]
-    float2* s_ml = reinterpret_cast<float2*>(reinterpret_cast<f32x4*>(s_kv) + HW * 64 * 64);
-    if (tg == 1) {
+  // The two token groups' results merged per head on the way out, through LDS (the tiles are
+  // free now): each group leaves half of its output tiles and its (reference max, sum) there,
+  // and finishes the other half: its own accumulators and the other group's from LDS, both
+  // rescaled to the larger reference.
+  f32x4* s_o = reinterpret_cast<f32x4*>(s_kv);  // [wave][HT * 4][64 lanes]
+  float2* s_ml = reinterpret_cast<float2*>(s_o + NW * HT * 4 * 64);
 #pragma unroll
-      for (int n = 0; n < NDV; ++n) {
+  for (int n = 0; n < HT; ++n)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          s_o[(n * 4 + q) * 64 + lane] =
-              f32x4{o[n][4 * q], o[n][4 * q + 1], o[n][4 * q + 2], o[n][4 * q + 3]};
-      }
-      if (lane < 32) s_ml[hg * 32 + col] = make_float2(m_run, l_run);
-    }
-    __syncthreads();
-    if (tg == 1) return;
-    const float2 other = s_ml[hg * 32 + col];
-    const float m_new = fmaxf(m_run, other.x);
-    // a group without a valid token has m = -inf, O = 0, l = 0 and contributes nothing
-    const float a0 = m_run == -INFINITY ? 0.f : exp2f(m_run - m_new);
-    const float a1 = other.x == -INFINITY ? 0.f : exp2f(other.x - m_new);
-    l_run = l_run * a0 + other.y * a1;
-    m_run = m_new;
-    const float l_inv = l_run > 0.f ? 1.f / l_run : 0.f;
-    if (head0 < a.H) {
-      // accumulator row 4q + e of a lane is head 8q + 4 half + e of the wave's 32
+    for (int q = 0; q < 4; ++q)
+      s_o[(wave * HT * 4 + n * 4 + q) * 64 + lane] =
+          f32x4{o[HT + n][4 * q], o[HT + n][4 * q + 1], o[HT + n][4 * q + 2], o[HT + n][4 * q + 3]};
+  if (lane < 32) s_ml[wave * 32 + col] = make_float2(m_run, l_run);
+  lds_barrier();
+  if (head0 >= a.H) return;
+  const int peer = wave ^ HW;  // the other token group's wave of these heads
+  const float2 g0 = s_ml[hg * 32 + col], g1 = s_ml[(HW + hg) * 32 + col];
+  const float m = fmaxf(g0.x, g1.x);
+  // a group without a valid token has m = -inf, O = 0, l = 0 and contributes nothing
+  const float a0 = g0.x == -INFINITY ? 0.f : exp2f(g0.x - m);
+  const float a1 = g1.x == -INFINITY ? 0.f : exp2f(g1.x - m);
+  const float l = g0.y * a0 + g1.y * a1;
+  const float l_inv = l > 0.f ? 1.f / l : 0.f;
+  // each head's scales to the lanes that hold its rows, by way of LDS (16-byte reads of four
+  // heads; lane permutes took 48 dependent LDS round trips)
+  float* s_w = reinterpret_cast<float*>(s_ml + 32 * NW) + wave * 96;
+  if (lane < 32) {
+    s_w[col] = tg == 0 ? a0 : a1;       // this group's
+    s_w[32 + col] = tg == 0 ? a1 : a0;  // the other group's
+    s_w[64 + col] = l_inv;
+  }
+  // accumulator row 4q + e of a lane is head 8q + 4 half + e of the wave's 32
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (8 * q >= n_head) break;
-        float s0[4], s1[4], inv[4];
+  for (int q = 0; q < 4; ++q) {
+    if (8 * q >= n_head) break;
+    const f32x4 sm = *reinterpret_cast<const f32x4*>(s_w + 8 * q + 4 * half);
+    const f32x4 sp = *reinterpret_cast<const f32x4*>(s_w + 32 + 8 * q + 4 * half);
+    const f32x4 inv = *reinterpret_cast<const f32x4*>(s_w + 64 + 8 * q + 4 * half);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s0[e] = __shfl(a0, 8 * q + 4 * half + e, 64);
-          s1[e] = __shfl(a1, 8 * q + 4 * half + e, 64);
-          inv[e] = __shfl(l_inv, 8 * q + 4 * half + e, 64);
-        }
+    for (int n = 0; n < HT; ++n) {
+      const f32x4 v = s_o[(peer * HT * 4 + n * 4 + q) * 64 + lane];
+      f32x4 r;
 #pragma unroll
-        for (int n = 0; n < NDV; ++n) {
-          const f32x4 v = s_o[(n * 4 + q) * 64 + lane];
-          f32x4 r;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            r[e] = acc(n, 4 * q + e) * s0[e] + v[e] * s1[e];
-          }
-          store(n, q, r, inv);
-        }
-      }
-    }
-  } else {
-    const float l_inv = l_run > 0.f ? 1.f / l_run : 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (8 * q >= n_head) break;
-      float inv[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) inv[e] = __shfl(l_inv, 8 * q + 4 * half + e, 64);
-#pragma unroll
-      for (int n = 0; n < NDV; ++n)
-        store(n, q, f32x4{acc(n, 4 * q), acc(n, 4 * q + 1), acc(n, 4 * q + 2), acc(n, 4 * q + 3)},
-              inv);
+      for (int e = 0; e < 4; ++e) r[e] = acc(n, 4 * q + e) * sm[e] + v[e] * sp[e];
+      store(n, q, r, inv);
     }
   }
-  if (!DIRECT && lane < 32 && head_ok)
-    a.part_ml[((int64_t)unit * a.n_parts + split) * a.H + head] = make_float2(m_run, l_run);
+  if (!DIRECT && tg == 0 && lane < 32 && head_ok)
+    a.part_ml[((int64_t)unit * a.n_parts + split) * a.H + head] = make_float2(m, l);
 }
 
 struct CombineArgs {
@@ -1173,11 +1217,11 @@ void launch_partial(const AttnArgs& args, hipStream_t stream) {
                      dim3(64 * HW * TW), 0, stream, args);
 }
 
-template <int HW, int TG, int NST, bool PACED = false, bool DIRECT = false>
+template <int HW, bool PACED = false, bool DIRECT = false>
 void launch_mla(const AttnArgs& args, hipStream_t stream) {
   const int nwg_pad = (args.n_wg + 7) & ~7;
-  hipLaunchKernelGGL((attn_mla_kernel<HW, TG, NST, PACED, DIRECT>), dim3(nwg_pad + args.rp.pf_wg),
-                     dim3(64 * HW * TG), 0, stream, args);
+  hipLaunchKernelGGL((attn_mla_kernel<HW, PACED, DIRECT>), dim3(nwg_pad + args.rp.pf_wg),
+                     dim3(128 * HW), 0, stream, args);
 }
 
 bool is_mla(const hisparse_attn_desc_t& d) {
@@ -1196,24 +1240,14 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   AttnPlan p{};
   p.n_tok = top_k * attn->tokens_per_record;
   if (is_mla(*attn)) {
-    // 32 heads per wave; up to 32 heads, 1 head wave and two token groups; above, 2 head waves (64
-    // heads) per workgroup. With 16 or more
-    // workgroup columns (units x head blocks) there are enough of them for two token groups per
-    // workgroup: twice the tokens per partial result at the same workgroup count, which halves
-    // the split partials (fp32, 2 KB per head) and the merge. Measured alone, attention + merge
-    // over units of 128 heads (us, best split count): 8 units 27.4 against 28.7, 16 units 34.5
-    // against 45.9 (one token group of 4 head waves, 16 splits), 32 units 50.8 against 55.5;
-    // below 8 units one token group is faster (2 units 18.7 against 20.7).
-    // With HISPARSE_ATTN_BESIDE_FETCH (another stream's host-link fetch shares the GPU) the
-    // same shapes take half as many workgroups (below): the other half of the CUs is left to
-    // the fetch's waves.
-    if (H <= 32) {
-      p.hw = 1;
-      p.tg = 2;
-    } else {
-      p.hw = 2;
-      p.tg = (int64_t)units * ((H + 63) / 64) >= 16 ? 2 : 1;
-    }
+    // 32 heads per wave, 1 head wave up to 32 heads, 2 (64 heads) above, and two token groups: the
+    // groups share a split's chunks in turn and a partial result covers both, so the split
+    // partials (fp32, 2 KB per head) are half of what one group's workgroups would write. With
+    // HISPARSE_ATTN_BESIDE_FETCH (another stream's host-link fetch shares the GPU) the same
+    // shapes take half as many workgroups (below): the other half of the CUs is left to the
+    // fetch's waves.
+    p.hw = H <= 32 ? 1 : 2;
+    p.tg = 2;
     p.tw = 1;
     p.hb = (H + 32 * p.hw - 1) / (32 * p.hw);
   } else {              // up to 64 heads per workgroup, 16 per wave
@@ -1241,7 +1275,7 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   // 1.82 and 3.43 ms unpaced against 1.241, 1.371, 1.519, 1.69 and 3.23 ms paced. At 16 columns
   // and below the chain of attention, merge and resolve is the longer one and the unpaced start
   // wins (16 requests: 1.005 against 1.052 ms; 8 requests: 0.711 against 0.724).
-  p.paced = is_mla(*attn) && (attn->flags & HISPARSE_ATTN_BESIDE_FETCH) && p.hw == 2 && p.tg == 2 &&
+  p.paced = is_mla(*attn) && (attn->flags & HISPARSE_ATTN_BESIDE_FETCH) && p.hw == 2 &&
             (int64_t)units * p.hb > 16;
   int splits;
   if (attn->num_splits > 0) {
@@ -1249,27 +1283,22 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   } else {
     // at most one workgroup per CU (a workgroup holds a CU's LDS, so one more would wait for a
     // second round), and enough chunks per split for the load pipeline to reach steady state.
-    // For latent attention with one token group the split partials (fp32, 2 KB per head and
-    // split) grow with the splits, and longer splits win as the grid gets more workgroup
-    // columns: 2 chunks per split up to 4 columns, 4 up to 16, 8 beyond (12 units of 128 heads:
-    // 39 against 55 us with 22 two-chunk splits).
     const int per_split = units * p.hb;
     splits = std::max(1, target / per_split);
-    int chunks_per_split = 4;
-    if (is_mla(*attn)) chunks_per_split = per_split <= 4 ? 2 : (per_split <= 16 ? 4 : 8);
+    // For latent attention the split partials and the merge grow with the splits: one chunk per
+    // token group up to 4 workgroup columns and from 16 on (where the grid limits the splits
+    // anyway), two between.
+    int split_chunks = is_mla(*attn) ? 2 : 4 * p.tw;  // 32-token chunks
+    if (is_mla(*attn) && per_split > 4 && per_split < 16) split_chunks = 4;
     // A call that carries a replay lasts as long as the replay's host reads; its attention only
     // has to finish within them, and the merge after it is on the decode chain. One request of
     // 128 heads with a replay of its 2048 selections into the next shared layer: 16 four-chunk
     // splits instead of 32 two-chunk ones take the launch from 28.0 to 27.4 us and its merge
     // from 5.8 to 4.6 us (one 1M-token request, 56 layers in groups of 4: decode step 2.299 ->
-    // 2.226 ms), although that attention alone takes 17.7 against 12.5 us.
-    if (is_mla(*attn) && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
-      chunks_per_split = std::max(chunks_per_split, 4);
-    // a call too small to give even 64 such workgroups is all latency: one chunk per split
-    if (is_mla(*attn) && (int64_t)per_split * (p.n_tok / (2 * chunk)) < 64) chunks_per_split = 1;
-    // two token groups: one workgroup per CU, however few chunks each group gets
-    if (is_mla(*attn) && p.tg == 2) chunks_per_split = 1;
-    const int min_work_splits = std::max(1, p.n_tok / (chunks_per_split * chunk));
+    // 2.226 ms), although that attention alone takes longer.
+    if (is_mla(*attn) && per_split < 16 && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
+      split_chunks = 4;
+    const int min_work_splits = std::max(1, p.n_tok / (split_chunks * kChunk));
     splits = std::max(1, std::min({splits, max_splits, min_work_splits}));
   }
   const int max_split_tokens = std::min(kMaxSplitRecords * attn->tokens_per_record, kMaxSplitTokens);
@@ -1332,20 +1361,21 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   a.hb = p.hb;
   a.n_parts = p.n_parts;
   a.n_wg = units * p.n_wg_splits * p.hb;
+  a.div_hb = make_fastdiv((uint32_t)p.hb);
+  a.div_splits = make_fastdiv((uint32_t)p.n_wg_splits);
+  a.div_idx = make_fastdiv((uint32_t)a.idx_units);
   a.scale_log2 = attn.scale * 1.4426950408889634f;
 
   // a unit that is one part needs no merge: the kernel writes the output itself
-  const bool direct = is_mla(attn) && p.tg == 2 && p.n_parts == 1 &&
-                      !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
+  const bool direct = is_mla(attn) && p.n_parts == 1 && !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
   a.out = out;
   if (is_mla(attn)) {
-    if (p.hw == 1 && direct) launch_mla<1, 2, 2, false, true>(a, stream);
-    else if (p.hw == 1) launch_mla<1, 2, 2>(a, stream);
-    else if (p.tg == 1) launch_mla<2, 1, 4>(a, stream);
-    else if (p.paced && direct) launch_mla<2, 2, 2, true, true>(a, stream);
-    else if (p.paced) launch_mla<2, 2, 2, true>(a, stream);
-    else if (direct) launch_mla<2, 2, 2, false, true>(a, stream);
-    else launch_mla<2, 2, 2>(a, stream);
+    if (p.hw == 1 && direct) launch_mla<1, false, true>(a, stream);
+    else if (p.hw == 1) launch_mla<1>(a, stream);
+    else if (p.paced && direct) launch_mla<2, true, true>(a, stream);
+    else if (p.paced) launch_mla<2, true>(a, stream);
+    else if (direct) launch_mla<2, false, true>(a, stream);
+    else launch_mla<2>(a, stream);
   } else {
     switch (p.hw) {
       case 1: launch_partial<128, 128, 128, 1, 4, 2>(a, stream); break;
