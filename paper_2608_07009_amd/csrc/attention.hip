@@ -7,7 +7,9 @@
 // Structure (every attention kernel: one workgroup per (unit, token split, head block); each
 // 32-token chunk is staged into LDS once with direct global->LDS loads and shared by the
 // workgroup's head waves)
-//   attn_partial_kernel  grouped-query records (d 128). A wave owns 16 query heads (the MFMA N
+//   attn_partial_kernel  grouped-query records (d 128), bound by HBM for large calls (64 units x 4
+//     heads x 4096 tokens, 134 MB: 36.3 us with one partial result per wave, 29.6 now, merge
+//     included; the copy rate gives 26) and by latency for small ones. A wave owns 16 query heads (the MFMA N
 //     dimension) and one 32-token chunk per iteration.
 //       S^T[token][head] = K[token][:] . Q^T[:][head]     v_mfma_f32_16x16x32_bf16, K from LDS
 //                                                        rows, Q resident in VGPRs
@@ -19,6 +21,8 @@
 //     in that order, so P never leaves the lane; the V operand is read in the same order.
 //   attn_mla_kernel  latent records (d_qk 576, d_v 512 = the key's first 512 dims): 32 heads
 //     per wave on v_mfma_f32_32x32x16_bf16, the output in accumulation registers.
+//   A workgroup's token groups (waves on different chunks of its split) are merged through LDS, so
+//     a split is one partial result; a unit that is one split is written out by the kernel.
 //   attn_combine_kernel / attn_combine_mla_kernel  merge the per-split (max, sum, unnormalised
 //     output) triples of each (unit, head) in ascending split order.
 //   Either attention kernel can carry an exact-prefetch replay: extra workgroups after the
@@ -67,6 +71,7 @@ struct AttnArgs {
   float* part_o;    // [units][n_parts][H][DV]
   float2* part_ml;  // [units][n_parts][H] (running max in log2 units, running sum)
   float* out;       // [units][H][DV]: the output, for the kernels that write it themselves
+  int32_t direct;   // grouped-query kernels: write the output, not partials (one split per unit)
   int64_t rec_per_unit;
   int32_t R, token_bytes, tpr_shift, k, H, n_tok;
   int32_t split_tokens, n_wg_splits, hb, n_parts, n_wg;
@@ -333,12 +338,19 @@ __device__ __forceinline__ void valid_words(uint32_t* s_valid, const int32_t* s_
 }
 
 // The calling wave's loads of the current chunk are done once at most `younger` (at most
-// NST - 2) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises.
-template <int NST, int LPW>
+// NST - 2) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises. With
+// one head wave per token group (HW = 1) the tiles are the wave's own and nobody waits for
+// another wave: the waves drift apart and one's loads overlap another's arithmetic.
+template <int N, bool BARRIER>
+__device__ __forceinline__ void wait_loads() {
+  if constexpr (BARRIER) wait_loads_and_barrier<N>();
+  else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+template <int NST, int LPW, int HW>
 __device__ __forceinline__ void wait_chunk(int younger) {
-  if (NST > 3 && younger >= 2) wait_loads_and_barrier<(NST > 3 ? 2 : 0) * LPW>();
-  else if (NST > 2 && younger >= 1) wait_loads_and_barrier<(NST > 2 ? 1 : 0) * LPW>();
-  else wait_loads_and_barrier<0>();
+  if (NST > 3 && younger >= 2) wait_loads<(NST > 3 ? 2 : 0) * LPW, (HW > 1)>();
+  else if (NST > 2 && younger >= 1) wait_loads<(NST > 2 ? 1 : 0) * LPW, (HW > 1)>();
+  else wait_loads<0, (HW > 1)>();
 }
 
 template <int DQK, int DV, int VOFF, int HW, int TW, int NST>
@@ -428,6 +440,7 @@ void attn_partial_kernel(AttnArgs a) {
   // every chunk the token groups iterate over gets its word, including chunks that lie wholly
   // past the split end
   valid_words<HW * TW>(s_valid, s_idx, rows, tok_begin, n_it * kChunk * TW);
+  if constexpr (HW == 1) lds_barrier();  // the loop has no barrier to publish the words
 #pragma unroll
   for (int st = 1; st < NST - 1; ++st)
     if (st < n_it) {
@@ -496,7 +509,7 @@ void attn_partial_kernel(AttnArgs a) {
   for (;;) {
     for (; it < n_it; ++it) {
       // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
-      wait_chunk<NST, LPW>(min(NST - 2, n_it - 1 - it));
+      wait_chunk<NST, LPW, HW>(min(NST - 2, n_it - 1 - it));
       const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
       // the chunk's validity word, read before the next chunk's loads are issued
       const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TW + tg]);
@@ -576,20 +589,66 @@ void attn_partial_kernel(AttnArgs a) {
   l_run += __shfl_xor(l_run, 16, 64);  // each lane summed its quarter of the head's weights
   l_run += __shfl_xor(l_run, 32, 64);
 
-  // ---- partial results of this (split, token group) ----
-  const int part = split * TW + tg;
-  float* po = a.part_o + ((int64_t)unit * a.n_parts + part) * a.H * DV;
-  const int head_base = hb * 16 * HW + hg * 16 + 4 * g;
+  // ---- results of this split: the token groups' results merged per head through LDS, in group
+  // order, each wave finishing NOUT / TW of its heads' output tiles. A split is then one partial
+  // result instead of one per token group, and a unit that is one split is written out here,
+  // as the merge of one part would (weight 1, one reciprocal). ----
+  constexpr int NF = NOUT / TW;
+  static_assert(NOUT % TW == 0 && TW * NST * T::BYTES >= TW * HW * (NOUT * 64 * 16 + 16 * 8),
+                "the tiles hold every wave's results");
+  f32x4* s_o = reinterpret_cast<f32x4*>(s_kv);  // [TW][HW][NOUT][64 lanes]
+  float2* s_ml = reinterpret_cast<float2*>(s_o + TW * HW * NOUT * 64);  // [TW][HW][16 heads]
+  lds_barrier();  // every wave is past its tiles
+#pragma unroll
+  for (int n = 0; n < NOUT; ++n) s_o[(wave * NOUT + n) * 64 + lane] = o[n];
+  if (lane < 16) s_ml[wave * 16 + lane] = make_float2(m_run, l_run);
+  lds_barrier();
+  // this lane's accumulator rows are heads 4g .. 4g + 3 of the wave's 16
+  float wt[TW][4], M[4], L[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int h = head_base + j;
-    if (h < a.H) {
+    float2 ml[TW];
+    M[j] = -INFINITY;
+    L[j] = 0.f;
 #pragma unroll
-      for (int n = 0; n < NOUT; ++n) po[(int64_t)h * DV + n * 16 + (lane & 15)] = o[n][j];
+    for (int t = 0; t < TW; ++t) {
+      ml[t] = s_ml[(t * HW + hg) * 16 + 4 * g + j];
+      M[j] = fmaxf(M[j], ml[t].x);
+    }
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      // a group without a valid token has m = -inf, O = 0, l = 0 and contributes nothing
+      wt[t][j] = ml[t].x == -INFINITY ? 0.f : exp2f(ml[t].x - M[j]);
+      L[j] += ml[t].y * wt[t][j];
     }
   }
-  if (lane < 16 && head_ok)
-    a.part_ml[((int64_t)unit * a.n_parts + part) * a.H + head] = make_float2(m_run, l_run);
+  const int head_base = hb * 16 * HW + hg * 16 + 4 * g;
+  float* po = a.direct ? a.out + (int64_t)unit * a.H * DV
+                       : a.part_o + ((int64_t)unit * a.n_parts + split) * a.H * DV;
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const int n = tg * NF + i;
+    f32x4 r = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      const f32x4 v = s_o[((t * HW + hg) * NOUT + n) * 64 + lane];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] += v[j] * wt[t][j];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int h = head_base + j;
+      const float inv = L[j] > 0.f ? 1.f / L[j] : 0.f;
+      if (h < a.H) po[(int64_t)h * DV + n * 16 + (lane & 15)] = a.direct ? r[j] * inv : r[j];
+    }
+  }
+  if (!a.direct && tg == 0 && (lane & 15) == 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (head_base + j < a.H)
+        a.part_ml[((int64_t)unit * a.n_parts + split) * a.H + head_base + j] =
+            make_float2(M[j], L[j]);
+  }
 }
 
 // Logical row r of a 32-token MFMA tile -> LDS tile row (token) for the latent-attention kernel.
@@ -1037,14 +1096,13 @@ struct CombineArgs {
   CarriedReplay rp;
 };
 
-// One wave per (unit, head): the largest partial reference max M, the weights
-// w_p = 2^(m_p - M), then out = sum_p w_p o_p / sum_p w_p l_p, over the parts in split order.
-// Lane j holds the weight of part j of each group of 64 parts; eight parts' outputs are in
-// flight at a time.
-template <int DV>
+// One wave per (unit, head) of grouped-query attention: the largest partial reference max M, the
+// weights w_p = 2^(m_p - M), then out = sum_p w_p o_p / sum_p w_p l_p, over the parts in split
+// order. Lane j holds the weight of part j of each group of 64 parts and two output floats; eight
+// parts' outputs are in flight at a time, the first eight while the weights are worked out (the
+// call is all latency: parts and weights one after the other took 0.9 us more).
 __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
-  constexpr int E = DV / 64;  // output floats per lane
-  static_assert(E == 2 || E == 8, "d_v");
+  constexpr int DV = 128;
   if ((int)blockIdx.x >= a.n_wg) {  // wave-uniform: the whole workgroup replays
     replay_worker(a.rp, (int)blockIdx.x - a.n_wg);
     return;
@@ -1056,45 +1114,41 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
   const int np = a.n_parts;
   const int64_t pstride = (int64_t)a.H * DV;
   const float2* ml = a.part_ml + (int64_t)unit * np * a.H + h;
-  const float* po = a.part_o + (int64_t)unit * np * pstride + (int64_t)h * DV + lane * E;
+  const float* po = a.part_o + (int64_t)unit * np * pstride + (int64_t)h * DV + lane * 2;
 
-  float M = -INFINITY;
-  for (int pb = lane; pb < np; pb += 64) M = fmaxf(M, ml[(int64_t)pb * a.H].x);
+  const float2 ml0 = ml[(int64_t)min(lane, np - 1) * a.H];  // this lane's part of the first 64
+  float2 val[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    val[u] = *reinterpret_cast<const float2*>(po + (int64_t)min(u, np - 1) * pstride);
+  float M = lane < np ? ml0.x : -INFINITY;
+  for (int pb = lane + 64; pb < np; pb += 64) M = fmaxf(M, ml[(int64_t)pb * a.H].x);
 #pragma unroll
   for (int x = 32; x >= 1; x >>= 1) M = fmaxf(M, __shfl_xor(M, x, 64));
 
-  float acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.f;
-  float lsum = 0.f;
+  float acc0 = 0.f, acc1 = 0.f, lsum = 0.f;
   for (int pb = 0; pb < np; pb += 64) {
     float w = 0.f;
     if (pb + lane < np) {
-      const float2 v = ml[(int64_t)(pb + lane) * a.H];
+      float2 v = ml0;
+      if (pb > 0) v = ml[(int64_t)(pb + lane) * a.H];
       w = v.x == -INFINITY ? 0.f : exp2f(v.x - M);
       lsum += w * v.y;
     }
     const int n = min(64, np - pb);
     for (int i = 0; i < n; i += 8) {
-      float val[8][E];
+      if (pb + i > 0) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (i + u < n) {
-          const float* src = po + (int64_t)(pb + i + u) * pstride;
-#pragma unroll
-          for (int e = 0; e < E; e += 2) {
-            const float2 t = *reinterpret_cast<const float2*>(src + e);
-            val[u][e] = t.x;
-            val[u][e + 1] = t.y;
-          }
-        }
+        for (int u = 0; u < 8; ++u)
+          val[u] = *reinterpret_cast<const float2*>(
+              po + (int64_t)(pb + min(i + u, n - 1)) * pstride);
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (i + u < n) {
           const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), i + u));
-#pragma unroll
-          for (int e = 0; e < E; ++e) acc[e] += wu * val[u][e];
+          acc0 += wu * val[u].x;
+          acc1 += wu * val[u].y;
         }
       }
     }
@@ -1102,10 +1156,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
   for (int x = 32; x >= 1; x >>= 1) lsum += __shfl_xor(lsum, x, 64);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-  float* dst = a.out + (int64_t)row * DV + lane * E;
-#pragma unroll
-  for (int e = 0; e < E; e += 2)
-    *reinterpret_cast<float2*>(dst + e) = make_float2(acc[e] * inv, acc[e + 1] * inv);
+  *reinterpret_cast<float2*>(a.out + (int64_t)row * DV + lane * 2) =
+      make_float2(acc0 * inv, acc1 * inv);
 }
 
 struct CombineMlaArgs {
@@ -1285,11 +1337,13 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // second round), and enough chunks per split for the load pipeline to reach steady state.
     const int per_split = units * p.hb;
     splits = std::max(1, target / per_split);
-    // For latent attention the split partials and the merge grow with the splits: one chunk per
-    // token group up to 4 workgroup columns and from 16 on (where the grid limits the splits
-    // anyway), two between.
-    int split_chunks = is_mla(*attn) ? 2 : 4 * p.tw;  // 32-token chunks
-    if (is_mla(*attn) && per_split > 4 && per_split < 16) split_chunks = 4;
+    // A round is one chunk per token group. Latent attention: the split partials and the merge
+    // grow with the splits: one round per split up to 4 workgroup columns and from 16 on (where
+    // the grid limits the splits anyway), two between. Grouped-query: two rounds per split; a
+    // round takes about 1 us, and 4 units x 4096 tokens take 10.9 us in 16 splits (two rounds each)
+    // against 11.8 in 8, 16 units x 2048 tokens 10.8 in 8 against 12.4 in 4.
+    int split_rounds = is_mla(*attn) ? 1 : 2;
+    if (is_mla(*attn) && per_split > 4 && per_split < 16) split_rounds = 2;
     // A call that carries a replay lasts as long as the replay's host reads; its attention only
     // has to finish within them, and the merge after it is on the decode chain. One request of
     // 128 heads with a replay of its 2048 selections into the next shared layer: 16 four-chunk
@@ -1297,9 +1351,14 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // from 5.8 to 4.6 us (one 1M-token request, 56 layers in groups of 4: decode step 2.299 ->
     // 2.226 ms), although that attention alone takes longer.
     if (is_mla(*attn) && per_split < 16 && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
-      split_chunks = 4;
-    const int min_work_splits = std::max(1, p.n_tok / (split_chunks * kChunk));
+      split_rounds = 2;
+    const int min_work_splits = std::max(1, p.n_tok / (split_rounds * chunk));
     splits = std::max(1, std::min({splits, max_splits, min_work_splits}));
+    // A grouped-query unit of one split needs no merge, a launch of its own that costs about 2.5
+    // us, against about 1 us for a round: 11 units x 501 tokens, four rounds, take 8.7 us in one
+    // split against 10.8 in two to four. (A latent round takes 2.1 us: one request of 16 heads
+    // over 128 tokens is no faster in one split of two rounds than in two and a merge.)
+    if (!is_mla(*attn) && max_splits <= 5) splits = 1;
   }
   const int max_split_tokens = std::min(kMaxSplitRecords * attn->tokens_per_record, kMaxSplitTokens);
   splits = std::max(splits, (p.n_tok + max_split_tokens - 1) / max_split_tokens);
@@ -1308,15 +1367,16 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   p.split_tokens = (per + chunk - 1) / chunk * chunk;
   if (p.split_tokens > max_split_tokens) p.split_tokens = max_split_tokens / chunk * chunk;
   p.n_wg_splits = (p.n_tok + p.split_tokens - 1) / p.split_tokens;
-  p.n_parts = p.n_wg_splits * p.tw;
+  p.n_parts = p.n_wg_splits;
   // the latent-attention merge holds one weight per part in LDS (hisparse_validate_attn keeps the
   // token count within reach of that limit)
   if (is_mla(*attn) && p.n_parts > kMlaMaxParts) return HISPARSE_ERR_UNSUPPORTED;
   const int64_t n_wg = (int64_t)units * p.n_wg_splits * p.hb;
   if (n_wg > (1LL << 30)) return HISPARSE_ERR_INVALID_ARG;
   const int h_store = is_mla(*attn) ? (H + 31) / 32 * 32 : H;
-  const size_t o_bytes = (size_t)units * p.n_parts * h_store * attn->d_v * sizeof(float);
-  const size_t ml_bytes = (size_t)units * p.n_parts * H * sizeof(float2);
+  // grouped-query sizes count one part per token group, as callers may have stored them
+  const size_t o_bytes = (size_t)units * p.n_parts * p.tw * h_store * attn->d_v * sizeof(float);
+  const size_t ml_bytes = (size_t)units * p.n_parts * p.tw * H * sizeof(float2);
   p.workspace_bytes = ((o_bytes + 255) & ~(size_t)255) + ml_bytes;
   *plan = p;
   return HISPARSE_OK;
@@ -1367,7 +1427,8 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   a.scale_log2 = attn.scale * 1.4426950408889634f;
 
   // a unit that is one part needs no merge: the kernel writes the output itself
-  const bool direct = is_mla(attn) && p.n_parts == 1 && !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
+  const bool direct = p.n_parts == 1 && !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
+  a.direct = direct;
   a.out = out;
   if (is_mla(attn)) {
     if (p.hw == 1 && direct) launch_mla<1, false, true>(a, stream);
@@ -1421,7 +1482,7 @@ hipError_t launch_merge(const AttnPlan& p, const hisparse_attn_desc_t& attn, int
   }
   CombineArgs c{part_o, part_ml, out, attn.q_heads, p.n_parts, units * attn.q_heads, 0, rp};
   c.n_wg = (units * attn.q_heads + 3) / 4;
-  hipLaunchKernelGGL(attn_combine_kernel<128>, dim3(c.n_wg + rp.pf_wg), dim3(256), 0, stream, c);
+  hipLaunchKernelGGL(attn_combine_kernel, dim3(c.n_wg + rp.pf_wg), dim3(256), 0, stream, c);
   return hipGetLastError();
 }
 
