@@ -35,6 +35,7 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kMaxChunk = 16;  // order entries per thread: B <= 16 * threads
+constexpr int kChunk = 4;      // and up to 4 * 1024 entries, 4 per thread
 constexpr int kMaxPer = 4;     // selections per thread: k <= 4 * threads
 constexpr int kBucketBits = 11;
 constexpr int kBuckets = 1 << kBucketBits;  // miss rank buckets (high position bits)
@@ -49,37 +50,50 @@ constexpr int kScanLimit = HISPARSE_SCAN_LIMIT;
 // outstanding host reads, not a whole workgroup's worth.
 constexpr int kFetchThreads = 64;
 
-__device__ inline int wave_incl_scan(int x, int lane) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    int y = __shfl_up(x, o, kWave);
-    if (lane >= o) x += y;
-  }
+// Wave-wide scan and reductions by DPP (data-parallel primitive) moves: within rows of 16 lanes by
+// shifts, then from row to row by broadcasts. Six dependent vector instructions, where lane
+// permutes through LDS are six round trips: the three scans and the position range of a resolve
+// took about 2.5 us of its 11.4 us (16 units, 1024 threads) that way.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_move(int identity, int x) {
+  return __builtin_amdgcn_update_dpp(identity, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x += dpp_move<0x111, 0xF>(0, x);  // row_shr:1
+  x += dpp_move<0x112, 0xF>(0, x);
+  x += dpp_move<0x114, 0xF>(0, x);
+  x += dpp_move<0x118, 0xF>(0, x);
+  x += dpp_move<0x142, 0xA>(0, x);  // row_bcast:15 into rows 1 and 3
+  x += dpp_move<0x143, 0xC>(0, x);  // row_bcast:31 into rows 2 and 3
   return x;
 }
-
-// Exclusive workgroup scan of v; *total = sum over the workgroup. s_tmp: NT/64 + 1 ints.
-// Starts and ends with a barrier-protected use of s_tmp.
-template <int NT>
-__device__ inline int block_excl_scan(int v, int* s_tmp, int* total) {
-  constexpr int NW = NT / kWave;
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int incl = wave_incl_scan(v, lane);
-  if (lane == kWave - 1) s_tmp[wid] = incl;
-  __syncthreads();
-  if (wid == 0) {
-    const int w = lane < NW ? s_tmp[lane] : 0;
-    const int wi = wave_incl_scan(w, lane);
-    if (lane < NW) s_tmp[lane] = wi - w;
-    if (lane == NW - 1) s_tmp[NW] = wi;
-  }
-  __syncthreads();
-  const int r = s_tmp[wid] + incl - v;
-  *total = s_tmp[NW];
-  __syncthreads();
-  return r;
+__device__ __forceinline__ int wave_min(int x) {
+  constexpr int I = INT32_MAX;
+  x = min(x, dpp_move<0x111, 0xF>(I, x));
+  x = min(x, dpp_move<0x112, 0xF>(I, x));
+  x = min(x, dpp_move<0x114, 0xF>(I, x));
+  x = min(x, dpp_move<0x118, 0xF>(I, x));
+  x = min(x, dpp_move<0x142, 0xA>(I, x));
+  x = min(x, dpp_move<0x143, 0xC>(I, x));
+  return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
+// Exclusive workgroup scan of v; *total = sum over the workgroup. s_tmp: NT/64 ints that nothing
+// else uses until the next barrier after the call. One barrier: every wave scans the waves' sums
+// for itself.
+template <int NT>
+__device__ __forceinline__ int block_excl_scan(int v, int* s_tmp, int* total) {
+  constexpr int NW = NT / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int incl = wave_incl_scan(v);
+  if (lane == kWave - 1) s_tmp[wid] = incl;
+  __syncthreads();
+  const int sums = wave_incl_scan(lane < NW ? s_tmp[lane] : 0);
+  *total = __builtin_amdgcn_readlane(sums, kWave - 1);
+  const int before = wid > 0 ? __builtin_amdgcn_readlane(sums, wid - 1) : 0;
+  return before + incl - v;
+}
 
 __device__ inline bool bit_test(const uint32_t* bm, int s) { return (bm[s >> 5] >> (s & 31)) & 1u; }
 
@@ -103,16 +117,22 @@ __device__ unsigned long long g_phase_stamps[kPhaseStampUnits * kPhaseStamps];
   } while (0)
 #endif
 
-template <int NT>
+// CH: recency entries per thread (B <= CH * NT), consecutive ones, read 16 bytes at a time where B
+// is a multiple of 4.
+template <int NT, int CH>
 __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  __shared__ int s_tmp[NT / kWave + 1];
+  __shared__ int s_tmp[3][NT / kWave];  // one per scan
   __shared__ int s_nmiss, s_bad;
   __shared__ int s_pmin, s_pmax, s_maxb;  // miss position range, largest bucket
 
   const int unit = blockIdx.x;
   const int tid = threadIdx.x;
   RESOLVE_STAMP(0);
+  // every argument in one round trip
+  asm volatile("" ::"s"(a.sel), "s"(a.pt), "s"(a.slot_pos), "s"(a.slot_ts), "s"(a.order),
+               "s"(a.clock), "s"(a.slots_out), "s"(a.counts_out), "s"(a.plan), "s"(a.plan_count),
+               "s"(a.L), "s"(a.B), "s"(a.k));
   const int k = a.k, B = a.B;
   const int64_t L = a.L;
   const int k4 = (k + 3) & ~3;
@@ -156,6 +176,36 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
   }
 #pragma unroll
   for (int u = 0; u < kMaxPer; ++u) sv[u] = (pv[u] >= 0 && (int64_t)pv[u] < L) ? pt[pv[u]] : -1;
+  const uint32_t t = a.clock[unit] + 1u;
+  // Phase 3's recency entries, issued behind the probes: loads return in order, so the probes'
+  // results are not held up by them, and they are here when phase 3 begins (0.8 us off its start
+  // with B = 4096). Only with one load per thread: four or more cost phase 1 what phase 3 gains.
+  const int ch = (B & 3) ? (B + NT - 1) / NT : ((B + NT - 1) / NT + 3) & ~3;
+  const int j0 = tid * ch;
+  int32_t ov[CH];
+  const bool vec = (B & 3) == 0;
+  auto read_order = [&]() {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) ov[c] = -1;
+    if (vec) {
+#pragma unroll
+      for (int c = 0; c < CH; c += 4)
+        if (c < ch && j0 + c < B) {
+          const int4 v = *reinterpret_cast<const int4*>(order + j0 + c);
+          ov[c] = v.x;
+          ov[c + 1] = v.y;
+          ov[c + 2] = v.z;
+          ov[c + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (c < ch && j0 + c < B) ov[c] = order[j0 + c];
+    }
+  };
+  if constexpr (CH == kChunk) {
+    if (vec) read_order();
+  }
   int pmin = INT32_MAX, pmax = -1;  // this thread's miss positions (phase 2 buckets by them)
 #pragma unroll
   for (int u = 0; u < kMaxPer; ++u) {
@@ -180,11 +230,8 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
       s_out[i] = out;
     }
   }
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    pmin = min(pmin, __shfl_xor(pmin, o, kWave));
-    pmax = max(pmax, __shfl_xor(pmax, o, kWave));
-  }
+  pmin = wave_min(pmin);
+  pmax = -1 - wave_min(-1 - pmax);  // -1 - x reverses the order within [-2^31, 2^31)
   if ((tid & (kWave - 1)) == 0 && pmax >= 0) {  // one LDS atomic pair per wave
     atomicMin(&s_pmin, pmin);
     atomicMax(&s_pmax, pmax);
@@ -247,7 +294,7 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
     }
     if (big > kScanLimit) atomicMax(&s_maxb, big);
     int total;
-    int run = block_excl_scan<NT>(sum, s_tmp, &total);  // all reads of s_cnt precede it
+    int run = block_excl_scan<NT>(sum, s_tmp[0], &total);  // all reads of s_cnt precede it
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int b = tid * per + q;
@@ -355,25 +402,16 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
     return;
   }
 
-  const uint32_t t = a.clock[unit] + 1u;
-
   // Phase 3a: victims = first m non-hit entries of the recency index.
-  const int ch = (B + NT - 1) / NT;
-  const int j0 = tid * ch;
-  int32_t ov[kMaxChunk];
+  if (CH != kChunk || !vec) read_order();
   int cnt = 0;
 #pragma unroll
-  for (int c = 0; c < kMaxChunk; ++c) {
-    ov[c] = -1;
-    if (c < ch && j0 + c < B) {
-      ov[c] = order[j0 + c];
-      cnt += bit_test(s_hit, ov[c]) ? 0 : 1;
-    }
-  }
+  for (int c = 0; c < CH; ++c)
+    if (ov[c] >= 0) cnt += bit_test(s_hit, ov[c]) ? 0 : 1;
   int total_nonhit;
-  int r = block_excl_scan<NT>(cnt, s_tmp, &total_nonhit);  // all reads of `order` precede it
+  int r = block_excl_scan<NT>(cnt, s_tmp[1], &total_nonhit);  // all reads of `order` precede it
 #pragma unroll
-  for (int c = 0; c < kMaxChunk; ++c) {
+  for (int c = 0; c < CH; ++c) {
     const int32_t s = ov[c];
     if (s >= 0 && !bit_test(s_hit, s)) {
       if (r < m) {
@@ -391,7 +429,7 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
   // Phase 3b: recency index tail (victims, then hits, each by slot) and hit stamps.
   int nv = 0, nh = 0;
 #pragma unroll
-  for (int c = 0; c < kMaxChunk; ++c) {
+  for (int c = 0; c < CH; ++c) {
     const int s = j0 + c;
     if (c < ch && s < B) {
       nv += bit_test(s_vic, s) ? 1 : 0;
@@ -399,12 +437,12 @@ __global__ __launch_bounds__(NT) void resolve_kernel(ResolveArgs a) {
     }
   }
   int packed_total;
-  const int base = block_excl_scan<NT>((nv << 16) | nh, s_tmp, &packed_total);
+  const int base = block_excl_scan<NT>((nv << 16) | nh, s_tmp[2], &packed_total);
   const int hits = packed_total & 0xFFFF;
   int rv = base >> 16, rh = base & 0xFFFF;
   const uint32_t ts_hit = 2u * t, ts_miss = 2u * t - 1u;
 #pragma unroll
-  for (int c = 0; c < kMaxChunk; ++c) {
+  for (int c = 0; c < CH; ++c) {
     const int s = j0 + c;
     if (c < ch && s < B) {
       if (bit_test(s_vic, s)) {
@@ -621,9 +659,9 @@ __global__ void reset_state_kernel(StateArgs a) {
   }
 }
 
-template <int NT>
+template <int NT, int CH = kChunk>
 hipError_t launch_resolve_nt(const ResolveArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(resolve_kernel<NT>, dim3(a.units), dim3(NT), resolve_lds_bytes(a.k, a.B),
+  hipLaunchKernelGGL((resolve_kernel<NT, CH>), dim3(a.units), dim3(NT), resolve_lds_bytes(a.k, a.B),
                      stream, a);
   return hipGetLastError();
 }
@@ -637,8 +675,7 @@ size_t resolve_lds_bytes(int32_t k, int32_t B) {
 
 int resolve_threads(int32_t B) {
   int nt = 64;
-  while (nt < 1024 && nt * kMaxChunk < B) nt <<= 1;
-  while (nt < 1024 && nt * 4 < B) nt <<= 1;  // about four order entries per thread
+  while (nt < 1024 && nt * kChunk < B) nt <<= 1;  // at most four order entries per thread
   return nt;
 }
 
@@ -650,7 +687,9 @@ hipError_t launch_resolve(const ResolveArgs& a, hipStream_t stream) {
     case 128: return launch_resolve_nt<128>(a, stream);
     case 256: return launch_resolve_nt<256>(a, stream);
     case 512: return launch_resolve_nt<512>(a, stream);
-    default: return launch_resolve_nt<1024>(a, stream);
+    default:
+      return a.B <= kChunk * 1024 ? launch_resolve_nt<1024>(a, stream)
+                                  : launch_resolve_nt<1024, kMaxChunk>(a, stream);
   }
 }
 
