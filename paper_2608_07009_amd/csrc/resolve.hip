@@ -571,10 +571,14 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
 // (no slot is hit, so none is exempt) with the miss stamp 2t-1, and the index rotates by one.
 // Then the unit's record of each of the group's layers is stored into that slot of the layer's
 // cache and at pos in the layer's host pool. The index is staged in LDS for the shift.
+// Bound: latency. The index entries, and the first record pieces, are read while the position's
+// page-table entry is on its way, sixteen index loads per thread at a time (one after the other,
+// an index of 4096 slots took 7 of the call's 10.9 us).
 __global__ __launch_bounds__(256) void admit_kernel(AdmitArgs a) {
   extern __shared__ uint16_t s_order[];  // [B] (slots < kMaxCapacity = 2^14)
   __shared__ int s_idx;
   typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+  constexpr int NT = 256, UN = 16;
   const int unit = blockIdx.x, grp = blockIdx.y, tid = threadIdx.x, B = a.B;
   const int anchor = a.first + grp * a.G;
   const AnchorState st = a.states[anchor / a.G];
@@ -605,15 +609,45 @@ __global__ __launch_bounds__(256) void admit_kernel(AdmitArgs a) {
   const int32_t hit = pt[p];
   if (tid == 0) s_idx = 0;  // stays in bounds even if the index were inconsistent
   __syncthreads();
-  for (int j = tid; j < B; j += blockDim.x) {
-    const int32_t s = order[j];
-    s_order[j] = (uint16_t)s;
-    if (s == hit) s_idx = j;  // the hit slot's place in the index (at most one thread)
+  for (int b = 0; b < B; b += NT * UN) {
+    int32_t v[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) v[u] = order[min(b + u * NT + tid, B - 1)];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int j = b + u * NT + tid;
+      if (j < B) {
+        s_order[j] = (uint16_t)v[u];
+        if (v[u] == hit) s_idx = j;  // the hit slot's place in the index (at most one thread)
+      }
+    }
+  }
+  // piece q of the group's records: layer anchor + q / pieces, 16 bytes each; this thread's first
+  const int cpr = a.R >> 4;
+  const int nz = min(anchor + a.G, a.first + a.n_layers) - anchor;
+  const int n_pieces = a.write ? nz * cpr : 0;
+  const v4u* records = reinterpret_cast<const v4u*>(a.records);
+  auto source = [&](int q, int z) {
+    return records + ((int64_t)(anchor + z - a.first) * a.units + unit) * cpr + (q - z * cpr);
+  };
+  v4u v0 = {};
+  LayerIO io0 = {};
+  int z0 = 0;
+  if (tid < n_pieces) {
+    z0 = tid / cpr;
+    v0 = *source(tid, z0);
+    io0 = a.layers[anchor + z0];
   }
   __syncthreads();
   const int idx = hit >= 0 ? s_idx : 0;  // the entry that moves to the most-recent end
   const int32_t slot = (int32_t)s_order[idx];
-  for (int j = idx + tid; j < B - 1; j += blockDim.x) order[j] = (int32_t)s_order[j + 1];
+  auto put = [&](int q, int z, const LayerIO& io, const v4u& v) {
+    const int64_t o = (int64_t)(q - z * cpr) << 4;
+    *reinterpret_cast<v4u*>(io.cache + ((int64_t)unit * B + slot) * a.R + o) = v;
+    *reinterpret_cast<v4u*>(io.host + ((int64_t)unit * a.L + p) * a.R + o) = v;
+  };
+  if (tid < n_pieces) put(tid, z0, io0, v0);
+  for (int j = idx + tid; j < B - 1; j += NT) order[j] = (int32_t)s_order[j + 1];
   if (tid == 0) {
     order[B - 1] = slot;
     if (hit >= 0) {
@@ -628,17 +662,9 @@ __global__ __launch_bounds__(256) void admit_kernel(AdmitArgs a) {
     *slot_out = slot;
     st.clock[unit] = t;
   }
-  if (!a.write) return;
-  const int z_end = min(anchor + a.G, a.first + a.n_layers);
-  for (int z = anchor; z < z_end; ++z) {
-    const uint8_t* src = a.records + ((int64_t)(z - a.first) * a.units + unit) * a.R;
-    uint8_t* cache = a.layers[z].cache + ((int64_t)unit * B + slot) * a.R;
-    uint8_t* host = a.layers[z].host + ((int64_t)unit * a.L + p) * a.R;
-    for (int q = tid; q < (a.R >> 4); q += blockDim.x) {
-      const v4u v = *reinterpret_cast<const v4u*>(src + 16 * q);
-      *reinterpret_cast<v4u*>(cache + 16 * q) = v;
-      *reinterpret_cast<v4u*>(host + 16 * q) = v;
-    }
+  for (int q = tid + NT; q < n_pieces; q += NT) {
+    const int z = q / cpr;
+    put(q, z, a.layers[anchor + z], *source(q, z));
   }
 }
 
