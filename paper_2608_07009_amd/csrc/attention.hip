@@ -854,19 +854,7 @@ void attn_mla_kernel(AttnArgs a) {
   // split end
   valid_words<NW>(s_valid, s_idx, rows, tok_begin, n_it * TG * kChunk);
 
-  auto finish_chunk = [&](const uint8_t* tile) {
-    uint32_t pw[8];
-#pragma unroll
-    for (int j = 0; j < 16; j += 2)
-      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
-    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) l_run = add_weights(pw[j], l_run);
-    const bf16x8_t pa0 = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});
-    const bf16x8_t pa1 = __builtin_bit_cast(bf16x8_t, u32x4{pw[4], pw[5], pw[6], pw[7]});
+  auto finish_chunk = [&](const uint8_t* tile, int it) {
     // V operand by transpose reads: in each 16-lane group lane 4s+q addresses row
     // 16kb + 4s + half (+2 for the second read), columns 32n + 16 (col >> 4) + 4q .. +3; lane
     // t of the group then holds V[those rows][32n + 16 (col >> 4) + t], the k order of P.
@@ -897,7 +885,19 @@ void attn_mla_kernel(AttnArgs a) {
       vlo[i % VD] = lds_read_tr16_b64<OFF>(va[h][i & 1][0]);
       vhi[i % VD] = lds_read_tr16_b64<OFF>(va[h][i & 1][1]);
     };
-    static_for<VD>(vread);
+    static_for<VD>(vread);  // in flight while the weights are worked out
+    uint32_t pw[8];
+#pragma unroll
+    for (int j = 0; j < 16; j += 2)
+      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
+    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) l_run = add_weights(pw[j], l_run);
+    const bf16x8_t pa0 = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});
+    const bf16x8_t pa1 = __builtin_bit_cast(bf16x8_t, u32x4{pw[4], pw[5], pw[6], pw[7]});
     static_for<NM>([&](auto i) {
       // the reads issued after index i's pair: those of indices i+1 .. min(i+VD-1, NM-1)
       constexpr int later = NM - 1 - i < VD - 1 ? NM - 1 - i : VD - 1;
@@ -907,6 +907,9 @@ void attn_mla_kernel(AttnArgs a) {
       o[i % NDV] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i < NDV ? pa0 : pa1, vb, o[i % NDV],
                                                            0, 0, 0);
       if constexpr (i + VD < NM) vread(std::integral_constant<int, i + VD>{});
+      // the next iteration's chunk to issue: its rows are found in the MFMAs' shadow
+      if constexpr (i == NDV / 2)
+        if (it + NST < n_it) chunk_rows(src, s_idx, rows, chunk0 + (it + NST) * kChunk * TG, rg0);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -924,12 +927,21 @@ void attn_mla_kernel(AttnArgs a) {
     wait_loads_and_barrier<LPW>();
   }
   read_q();
+  if (n_it > 1) chunk_rows(src, s_idx, rows, chunk0 + kChunk * TG, rg0);
 
   for (int it = 0; it < n_it; ++it) {
     wait_loads_and_barrier<0>();
     const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
-    // the chunk's validity word, read before the next chunk's loads are issued
-    const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TG + tg]);
+    constexpr int KD = 4;
+    static_assert(KD == 4 && NKK > KD, "a ring of 4 reads, one address register each");
+    const int kr = mla_row(col);
+    uint32_t ka[4];  // piece 2 kk + half of k-steps kk, kk + 4, ...
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      ka[i] = lds_addr(tile + T::row(kr) + (((2 * i + half) ^ tile_swizzle(kr)) << 4));
+    u32x4 kbuf[KD];
+    static_for<KD>([&](auto kk) { kbuf[kk] = lds_read_b128<(kk / 4) * 1024>(ka[kk & 3]); });
+    const uint32_t valid = s_valid[it * TG + tg];  // the chunk's validity word
     __builtin_amdgcn_sched_barrier(0);
     // Every wave is past its reads of buffer (it-1) % NST: it takes chunk it+NST-1, whose loads
     // go out LPI at a time between the score MFMAs. Issued in one run they would hold the wave
@@ -937,7 +949,6 @@ void attn_mla_kernel(AttnArgs a) {
     // for a chunk of each token group, with the MFMAs waiting behind it.
     const bool more = it + NST - 1 < n_it;
     uint8_t* next = s_tiles + ((it + NST - 1) % NST) * T::BYTES;
-    if (more) chunk_rows(src, s_idx, rows, chunk0 + (it + NST - 1) * kChunk * TG, rg0);
 
     // ---- scores: S^T for the chunk's 32 tokens x this wave's 32 heads ----
     // K operand reads run KD k-steps ahead of the MFMAs (a small register ring; the
@@ -948,16 +959,7 @@ void attn_mla_kernel(AttnArgs a) {
     // last one before the scores are read.
     constexpr int LPI = 3;  // one branch for three loads
     static_assert(LPW % LPI == 0 && LPW <= NKK, "the chunk's loads fit between the MFMAs");
-    constexpr int KD = 4;
-    static_assert(KD == 4 && NKK > KD, "a ring of 4 reads, one address register each");
     f32x16 sacc, sacc1;  // even / odd k-steps: two independent MFMA chains
-    const int kr = mla_row(col);
-    uint32_t ka[4];  // piece 2 kk + half of k-steps kk, kk + 4, ...
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      ka[i] = lds_addr(tile + T::row(kr) + (((2 * i + half) ^ tile_swizzle(kr)) << 4));
-    u32x4 kbuf[KD];
-    static_for<KD>([&](auto kk) { kbuf[kk] = lds_read_b128<(kk / 4) * 1024>(ka[kk & 3]); });
     static_for<NKK>([&](auto kk) {
       // the K reads issued after read kk: those of k-steps kk+1 .. min(kk+KD-1, NKK-1)
       constexpr int later = NKK - 1 - kk < KD - 1 ? NKK - 1 - kk : KD - 1;
@@ -977,6 +979,7 @@ void attn_mla_kernel(AttnArgs a) {
     sacc += sacc1;
 #pragma unroll
     for (int j = 0; j < 16; ++j) sc[j] = sacc[j];
+    const uint32_t vmask = __builtin_amdgcn_readfirstlane(valid);
     if (vmask != 0xFFFFFFFFu) {  // uniform: a chunk with padding
       int hq = half;
       asm volatile("" : "+v"(hq));
@@ -997,7 +1000,7 @@ void attn_mla_kernel(AttnArgs a) {
       if (m_run == -INFINITY) m_run = both;
     }
     if (__ballot(cmax > m_run + kMlaSlack) && lane == 0) s_fallback = 1;
-    finish_chunk(tile);
+    finish_chunk(tile, it);
   }
   l_run += __shfl_xor(l_run, 32, 64);  // each lane summed its half of the head's weights
   wait_loads_and_barrier<0>();  // no staging in flight; s_fallback is final
