@@ -744,6 +744,11 @@ void attn_mla_kernel(AttnArgs a) {
   static_assert(HW == 1 || HW == 2, "one query tile per token group at most");
   constexpr int RGW = 4 / HW;                // row groups of a chunk that one head wave stages
   constexpr int LPW = RGW * T::NSEG;         // its loads per chunk
+  // With one head wave a tile is its wave's own: no barrier in the loop, and the scores begin when
+  // the first four of a chunk's nine segments are here, the others being awaited in their middle
+  // (64 units of 16 heads: 42.1 us -> 40.8). With two, the second barrier costs what it saves (96
+  // units of 128 heads: 87.3 us against 88.5).
+  constexpr int EARLY = HW == 1 ? 4 : T::NSEG;
   constexpr int NKK = DQK / 16;  // QK k-steps
   constexpr int NDV = DV / 32;   // PV output tiles
   static_assert(LPW < 64, "the wait counter's range");
@@ -835,9 +840,13 @@ void attn_mla_kernel(AttnArgs a) {
   // spreads the workgroups' start-up traffic.
   if constexpr (!PACED) stage_q();
   const uint8_t* src[RGW];  // this lane's rows of the chunk to issue next
+  // Load l of a chunk: with one head wave segment by segment, else row group by row group.
+  auto stage = [&](auto l, uint8_t* tile) {
+    constexpr int seg = HW == 1 ? l / RGW : l % T::NSEG, i = HW == 1 ? l % RGW : l / T::NSEG;
+    stage_block<DQK / 8, seg>(tile, rg0 + i, src[i]);
+  };
   first_rows(src, entry0, rows, chunk0, rg0);
-#pragma unroll
-  for (int i = 0; i < RGW; ++i) stage_rows<DQK / 8>(s_tiles, rg0 + i, src[i]);
+  static_for<LPW>([&](auto l) { stage(l, s_tiles); });
   ic.store(s_idx, rows, n_rec);
   if (tid == 0) s_fallback = 0;
   f32x16 o[NDV];
@@ -927,10 +936,11 @@ void attn_mla_kernel(AttnArgs a) {
     wait_loads_and_barrier<LPW>();
   }
   read_q();
+  if constexpr (HW == 1) lds_barrier();  // both groups have the query: its buffer is free
   if (n_it > 1) chunk_rows(src, s_idx, rows, chunk0 + kChunk * TG, rg0);
 
   for (int it = 0; it < n_it; ++it) {
-    wait_loads_and_barrier<0>();
+    wait_loads<(T::NSEG - EARLY) * RGW, (HW > 1)>();
     const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
     constexpr int KD = 4;
     static_assert(KD == 4 && NKK > KD, "a ring of 4 reads, one address register each");
@@ -959,6 +969,8 @@ void attn_mla_kernel(AttnArgs a) {
     // last one before the scores are read.
     constexpr int LPI = 3;  // one branch for three loads
     static_assert(LPW % LPI == 0 && LPW <= NKK, "the chunk's loads fit between the MFMAs");
+    constexpr int KLATE = 4 * EARLY - KD;  // the k-step before the first read of a later segment
+    constexpr int ISSUED = (KLATE / LPI + 1) * LPI;  // the next chunk's loads that are out by then
     f32x16 sacc, sacc1;  // even / odd k-steps: two independent MFMA chains
     static_for<NKK>([&](auto kk) {
       // the K reads issued after read kk: those of k-steps kk+1 .. min(kk+KD-1, NKK-1)
@@ -967,9 +979,12 @@ void attn_mla_kernel(AttnArgs a) {
       if constexpr (kk % LPI == 0 && kk < LPW) {
         if (more)
           static_for<LPI>([&](auto i) {
-            constexpr int l = kk + i;
-            stage_block<DQK / 8, l % T::NSEG>(next, rg0 + l / T::NSEG, src[l / T::NSEG]);
+            stage(std::integral_constant<int, kk + i>{}, next);
           });
+      }
+      if constexpr (EARLY < T::NSEG && kk == KLATE) {
+        if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ISSUED) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
       if constexpr (kk + KD < NKK)
         kbuf[kk % KD] = lds_read_b128<((kk + KD) / 4) * 1024>(ka[kk & 3]);
