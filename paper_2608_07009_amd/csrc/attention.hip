@@ -338,7 +338,7 @@ __device__ __forceinline__ void valid_words(uint32_t* s_valid, const int32_t* s_
 }
 
 // The calling wave's loads of the current chunk are done once at most `younger` (at most
-// NST - 2) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises. With
+// NST - 2, none with one buffer) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises. With
 // one head wave per token group (HW = 1) the tiles are the wave's own and nobody waits for
 // another wave: the waves drift apart and one's loads overlap another's arithmetic.
 template <int N, bool BARRIER>
@@ -363,7 +363,8 @@ void attn_partial_kernel(AttnArgs a) {
   constexpr int NKK = DQK / 32;
   constexpr int NOUT = DV / 16;
   static_assert(DQK % 32 == 0 && DV % 16 == 0 && VOFF % 8 == 0, "shape");
-  static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPW < 64, "pipeline depth");
+  static_assert(NST >= 1 && NST <= 4 && (NST - 2) * LPW < 64, "pipeline depth");
+  static_assert(NST > 1 || HW == 1, "one round (NST = 1): a split of at most TW chunks");
   __shared__ __align__(1024) uint8_t s_kv[TW * NST * T::BYTES];
   __shared__ int32_t s_idx[kMaxSplitRecords];  // the split's record indices, -1 = skip
   __shared__ uint32_t s_valid[kMaxSplitTokens / 32];  // bit t of word c: token 32c+t attends
@@ -506,84 +507,100 @@ void attn_partial_kernel(AttnArgs a) {
     });
   };
 
-  for (;;) {
-    for (; it < n_it; ++it) {
-      // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
-      wait_chunk<NST, LPW, HW>(min(NST - 2, n_it - 1 - it));
-      const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
-      // the chunk's validity word, read before the next chunk's loads are issued
-      const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TW + tg]);
+  // the chunk's scores (sc, this lane's largest in cmax), and the head's reference max if it has
+  // none yet
+  auto scores = [&](const uint8_t* tile, uint32_t vmask) {
+    // ---- scores: S^T tiles for tokens [0,16) and [16,32) of the chunk ----
+    // K reads KD k-steps ahead (opaque LDS reads, see lds_read_b128), each k-step's MFMAs once
+    // its pair is in
+    s0 = f32x4{0.f, 0.f, 0.f, 0.f};
+    s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kr = tile_row(lane & 15);
+    const uint32_t krow = lds_addr(tile + T::row(kr));
+    const int kp = (g ^ tile_swizzle(kr)) << 4;  // piece 4 kk + g: kk odd is 64 bytes apart
+    const uint32_t ka_even = krow + kp, ka_odd = krow + (kp ^ 64);
+    constexpr int KD = 4;  // read pairs in flight
+    static_assert(KD <= NKK && 2 * KD <= 15, "lgkmcnt holds at most 15 outstanding reads");
+    u32x4 ka[KD], kb[KD];
+    auto kread = [&](auto kk) {
+      const uint32_t ad = (kk & 1) ? ka_odd : ka_even;
+      ka[kk % KD] = lds_read_b128<(kk / 2) * 1024>(ad);
+      kb[kk % KD] = lds_read_b128<(kk / 2) * 1024 + 2 * T::NSEG * 1024>(ad);
+    };
+    static_for<KD>(kread);
+    static_for<NKK>([&](auto kk) {
+      // the pairs issued after pair kk: those of k-steps kk+1 .. min(kk+KD-1, NKK-1)
+      constexpr int later = NKK - 1 - kk < KD - 1 ? NKK - 1 - kk : KD - 1;
+      lgkm_wait2<2 * later>(ka[kk % KD], kb[kk % KD]);
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk % KD]),
+                                                  qreg[kk], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kb[kk % KD]),
+                                                  qreg[kk], s1, 0, 0, 0);
+      if constexpr (kk + KD < NKK) kread(std::integral_constant<int, kk + KD>{});
       __builtin_amdgcn_sched_barrier(0);
-      // every wave is past its reads of buffer (it-1) % NST: refill it with chunk it+NST-1
-      if (it + NST - 1 < n_it) {
-        next_rows(it + NST - 1);
-        issue((it + NST - 1) % NST);
+    });
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sc[j] = j < 4 ? s0[j] : s1[j - 4];
+    if (vmask != 0xFFFFFFFFu) {  // uniform: a chunk with padding
+      int gq = g;
+      asm volatile("" : "+v"(gq));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int bit = j < 4 ? tile_row(4 * gq + j) : 16 + tile_row(4 * gq + (j - 4));
+        sc[j] = ((vmask >> bit) & 1u) ? sc[j] : -INFINITY;
       }
+    }
+    cmax = sc[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) cmax = fmaxf(cmax, sc[j]);
+    cmax *= a.scale_log2;  // this lane's quarter of the head's scores
+    // Validity is per token, so every head of the wave agrees on whether m_run is -inf.
+    // While it is, O and l are exactly zero and the reference max can simply be set.
+    if (__ballot(m_run == -INFINITY)) {
+      const float all = head_max(cmax);
+      if (m_run == -INFINITY) m_run = all;
+    }
+  };
 
-      // ---- scores: S^T tiles for tokens [0,16) and [16,32) of the chunk ----
-      // all K reads first (opaque LDS reads, see lds_read_b128), then each k-step's MFMAs once
-      // its pair is in
-      s0 = f32x4{0.f, 0.f, 0.f, 0.f};
-      s1 = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int kr = tile_row(lane & 15);
-      const uint32_t krow = lds_addr(tile + T::row(kr));
-      const int kp = (g ^ tile_swizzle(kr)) << 4;  // piece 4 kk + g: kk odd is 64 bytes apart
-      const uint32_t ka_even = krow + kp, ka_odd = krow + (kp ^ 64);
-      static_assert(NKK <= 8, "lgkmcnt holds at most 15 outstanding reads");
-      u32x4 ka[NKK], kb[NKK];
-      static_for<NKK>([&](auto kk) {
-        const uint32_t ad = (kk & 1) ? ka_odd : ka_even;
-        ka[kk] = lds_read_b128<(kk / 2) * 1024>(ad);
-        kb[kk] = lds_read_b128<(kk / 2) * 1024 + 2 * T::NSEG * 1024>(ad);
-      });
-      static_for<NKK>([&](auto kk) {
-        lgkm_wait2<2 * (NKK - 1 - kk)>(ka[kk], kb[kk]);
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk]),
-                                                    qreg[kk], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kb[kk]),
-                                                    qreg[kk], s1, 0, 0, 0);
+  if constexpr (NST == 1) {  // one round: no later chunk to wait for or to outgrow the reference
+    wait_chunk<NST, LPW, HW>(0);
+    scores(s_tiles, __builtin_amdgcn_readfirstlane(s_valid[tg]));
+    finish_chunk(s_tiles);
+  } else {
+    for (;;) {
+      for (; it < n_it; ++it) {
+        // chunks it+1 .. it+NST-2 were issued earlier and may still be in flight
+        wait_chunk<NST, LPW, HW>(min(NST - 2, n_it - 1 - it));
+        const uint8_t* tile = s_tiles + (it % NST) * T::BYTES;
+        // the chunk's validity word, read before the next chunk's loads are issued
+        const uint32_t vmask = __builtin_amdgcn_readfirstlane(s_valid[it * TW + tg]);
         __builtin_amdgcn_sched_barrier(0);
-      });
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sc[j] = j < 4 ? s0[j] : s1[j - 4];
-      if (vmask != 0xFFFFFFFFu) {  // uniform: a chunk with padding
-        int gq = g;
-        asm volatile("" : "+v"(gq));
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int bit = j < 4 ? tile_row(4 * gq + j) : 16 + tile_row(4 * gq + (j - 4));
-          sc[j] = ((vmask >> bit) & 1u) ? sc[j] : -INFINITY;
+        // every wave is past its reads of buffer (it-1) % NST: refill it with chunk it+NST-1
+        if (it + NST - 1 < n_it) {
+          next_rows(it + NST - 1);
+          issue((it + NST - 1) % NST);
         }
+        scores(tile, vmask);
+        if (__ballot(cmax > m_run + kRescaleSlack)) break;
+        finish_chunk(tile);
       }
-      cmax = sc[0];
+      if (it >= n_it) break;
+      // rare path: move the reference max of the heads whose scores outgrew it
+      const float m_new = fmaxf(m_run, head_max(cmax));
+      const float alpha = m_run == -INFINITY ? 1.f : exp2f(m_run - m_new);  // -inf: l and O are 0
+      l_run *= alpha;
+      m_run = m_new;
+      float al[4];
 #pragma unroll
-      for (int j = 1; j < 8; ++j) cmax = fmaxf(cmax, sc[j]);
-      cmax *= a.scale_log2;  // this lane's quarter of the head's scores
-      // Validity is per token, so every head of the wave agrees on whether m_run is -inf.
-      // While it is, O and l are exactly zero and the reference max can simply be set.
-      if (__ballot(m_run == -INFINITY)) {
-        const float all = head_max(cmax);
-        if (m_run == -INFINITY) m_run = all;
+      for (int j = 0; j < 4; ++j) al[j] = __shfl(alpha, 4 * g + j, 64);
+#pragma unroll
+      for (int n = 0; n < NOUT; ++n) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[n][j] *= al[j];
       }
-      if (__ballot(cmax > m_run + kRescaleSlack)) break;
-      finish_chunk(tile);
+      finish_chunk(s_tiles + (it % NST) * T::BYTES);
+      ++it;
     }
-    if (it >= n_it) break;
-    // rare path: move the reference max of the heads whose scores outgrew it
-    const float m_new = fmaxf(m_run, head_max(cmax));
-    const float alpha = m_run == -INFINITY ? 1.f : exp2f(m_run - m_new);  // -inf: l and O are 0
-    l_run *= alpha;
-    m_run = m_new;
-    float al[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) al[j] = __shfl(alpha, 4 * g + j, 64);
-#pragma unroll
-    for (int n = 0; n < NOUT; ++n) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o[n][j] *= al[j];
-    }
-    finish_chunk(s_tiles + (it % NST) * T::BYTES);
-    ++it;
   }
 
   l_run += __shfl_xor(l_run, 16, 64);  // each lane summed its quarter of the head's weights
@@ -1114,13 +1131,15 @@ struct CombineArgs {
   CarriedReplay rp;
 };
 
-// One wave per (unit, head) of grouped-query attention: the largest partial reference max M, the
-// weights w_p = 2^(m_p - M), then out = sum_p w_p o_p / sum_p w_p l_p, over the parts in split
-// order. Lane j holds the weight of part j of each group of 64 parts and two output floats; eight
-// parts' outputs are in flight at a time, the first eight while the weights are worked out (the
-// call is all latency: parts and weights one after the other took 0.9 us more).
+// One wave per (unit, head) of partials stored row by row: the largest partial reference max M,
+// the weights w_p = 2^(m_p - M), then out = sum_p w_p o_p / sum_p w_p l_p, over the parts in split
+// order. Lane j holds the weight of part j of each group of 64 parts and DV / 64 output floats;
+// eight parts' outputs are in flight at a time, the first eight while the weights are worked out
+// (the call is all latency: parts and weights one after the other took 0.9 us more).
+template <int DV>
 __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
-  constexpr int DV = 128;
+  constexpr int E = DV / 64;  // output floats per lane
+  typedef float vec __attribute__((ext_vector_type(E)));
   if ((int)blockIdx.x >= a.n_wg) {  // wave-uniform: the whole workgroup replays
     replay_worker(a.rp, (int)blockIdx.x - a.n_wg);
     return;
@@ -1132,19 +1151,20 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
   const int np = a.n_parts;
   const int64_t pstride = (int64_t)a.H * DV;
   const float2* ml = a.part_ml + (int64_t)unit * np * a.H + h;
-  const float* po = a.part_o + (int64_t)unit * np * pstride + (int64_t)h * DV + lane * 2;
+  const float* po = a.part_o + (int64_t)unit * np * pstride + (int64_t)h * DV + lane * E;
 
   const float2 ml0 = ml[(int64_t)min(lane, np - 1) * a.H];  // this lane's part of the first 64
-  float2 val[8];
+  vec val[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u)
-    val[u] = *reinterpret_cast<const float2*>(po + (int64_t)min(u, np - 1) * pstride);
+    val[u] = *reinterpret_cast<const vec*>(po + (int64_t)min(u, np - 1) * pstride);
   float M = lane < np ? ml0.x : -INFINITY;
   for (int pb = lane + 64; pb < np; pb += 64) M = fmaxf(M, ml[(int64_t)pb * a.H].x);
 #pragma unroll
   for (int x = 32; x >= 1; x >>= 1) M = fmaxf(M, __shfl_xor(M, x, 64));
 
-  float acc0 = 0.f, acc1 = 0.f, lsum = 0.f;
+  vec acc = {};
+  float lsum = 0.f;
   for (int pb = 0; pb < np; pb += 64) {
     float w = 0.f;
     if (pb + lane < np) {
@@ -1158,15 +1178,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
       if (pb + i > 0) {
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          val[u] = *reinterpret_cast<const float2*>(
+          val[u] = *reinterpret_cast<const vec*>(
               po + (int64_t)(pb + min(i + u, n - 1)) * pstride);
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (i + u < n) {
           const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), i + u));
-          acc0 += wu * val[u].x;
-          acc1 += wu * val[u].y;
+          acc += wu * val[u];
         }
       }
     }
@@ -1174,8 +1193,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(CombineArgs a) {
 #pragma unroll
   for (int x = 32; x >= 1; x >>= 1) lsum += __shfl_xor(lsum, x, 64);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-  *reinterpret_cast<float2*>(a.out + (int64_t)row * DV + lane * 2) =
-      make_float2(acc0 * inv, acc1 * inv);
+  *reinterpret_cast<vec*>(a.out + (int64_t)row * DV + lane * E) = acc * inv;
 }
 
 struct CombineMlaArgs {
@@ -1316,18 +1334,25 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // HISPARSE_ATTN_BESIDE_FETCH (another stream's host-link fetch shares the GPU) the same
     // shapes take half as many workgroups (below): the other half of the CUs is left to the
     // fetch's waves.
+    // Up to 16 heads over at most 128 tokens, the grouped-query kernel's shape: 16 heads per wave,
+    // four waves on a chunk each, merged in the workgroup, no merge launch: 10.1 us against 11.8
+    // (1 unit) and 10.8 against 13.1 (64 units). Beyond one round it loses what it saves: its
+    // tiles leave no room for the next chunk (256 tokens 12.2 against 11.5 in four splits, 64
+    // units x 2048 tokens 44.9 against 40.8).
+    p.rows = H <= 16 && p.n_tok <= 4 * kChunk;
     p.hw = H <= 32 ? 1 : 2;
-    p.tg = 2;
-    p.tw = 1;
+    p.tg = p.rows ? 1 : 2;
+    p.tw = p.rows ? 4 : 1;
     p.hb = (H + 32 * p.hw - 1) / (32 * p.hw);
   } else {              // up to 64 heads per workgroup, 16 per wave
     p.hw = H > 32 ? 4 : (H > 16 ? 2 : 1);
     p.tw = 4 / p.hw;
     p.tg = 1;
+    p.rows = true;
     p.hb = (H + 16 * p.hw - 1) / (16 * p.hw);
   }
   // a split is a whole number of the workgroup's chunk rounds
-  const int chunk = kChunk * (is_mla(*attn) ? p.tg : p.tw);
+  const int chunk = kChunk * p.tg * p.tw;
   const int max_splits = (p.n_tok + chunk - 1) / chunk;
   // Beside another stream's host-link fetch, latent attention aims at half a workgroup per CU:
   // the fetch's waves, whose slow host reads occupy the memory pipelines of the CUs they run
@@ -1393,8 +1418,9 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   if (n_wg > (1LL << 30)) return HISPARSE_ERR_INVALID_ARG;
   const int h_store = is_mla(*attn) ? (H + 31) / 32 * 32 : H;
   // grouped-query sizes count one part per token group, as callers may have stored them
-  const size_t o_bytes = (size_t)units * p.n_parts * p.tw * h_store * attn->d_v * sizeof(float);
-  const size_t ml_bytes = (size_t)units * p.n_parts * p.tw * H * sizeof(float2);
+  const int per_part = is_mla(*attn) ? 1 : p.tw;
+  const size_t o_bytes = (size_t)units * p.n_parts * per_part * h_store * attn->d_v * sizeof(float);
+  const size_t ml_bytes = (size_t)units * p.n_parts * per_part * H * sizeof(float2);
   p.workspace_bytes = ((o_bytes + 255) & ~(size_t)255) + ml_bytes;
   *plan = p;
   return HISPARSE_OK;
@@ -1412,7 +1438,7 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
     // replay and attention never share a CU's memory pipeline)
     const int64_t n_attn = (int64_t)units * p.n_wg_splits * p.hb;
     const int64_t idle = std::max<int64_t>(0, kTargetWorkgroups - ((n_attn + 7) & ~7LL));
-    if (!carried_replay(*prefetch, 64 * p.hw * (is_mla(attn) ? p.tg : p.tw), idle,
+    if (!carried_replay(*prefetch, 64 * p.hw * p.tg * p.tw, idle,
                         prefetch_threads, prefetch_block_bytes, &a.rp))
       return hipErrorInvalidValue;
   }
@@ -1420,7 +1446,7 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   a.pool = pool;
   a.q = q;
   a.idx = idx;
-  a.Hp = is_mla(attn) ? (attn.q_heads + 31) / 32 * 32 : attn.q_heads;
+  a.Hp = p.rows ? attn.q_heads : (attn.q_heads + 31) / 32 * 32;
   const size_t o_bytes = (size_t)units * p.n_parts * a.Hp * attn.d_v * sizeof(float);
   a.part_o = reinterpret_cast<float*>(workspace);
   a.part_ml = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(workspace) +
@@ -1448,7 +1474,10 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   const bool direct = p.n_parts == 1 && !(attn.flags & HISPARSE_ATTN_DEFER_MERGE);
   a.direct = direct;
   a.out = out;
-  if (is_mla(attn)) {
+  if (is_mla(attn) && p.rows) {
+    if (p.split_tokens > 4 * kChunk) return hipErrorInvalidValue;  // the plan's: one round
+    launch_partial<576, 512, 0, 1, 4, 1>(a, stream);
+  } else if (is_mla(attn)) {
     if (p.hw == 1 && direct) launch_mla<1, false, true>(a, stream);
     else if (p.hw == 1) launch_mla<1>(a, stream);
     else if (p.paced && direct) launch_mla<2, true, true>(a, stream);
@@ -1473,7 +1502,7 @@ hipError_t launch_merge(const AttnPlan& p, const hisparse_attn_desc_t& attn, int
                         const FetchArgs* prefetch, int32_t prefetch_threads,
                         int32_t prefetch_block_bytes) {
   // the same workspace layout as launch_attention: partial outputs, then (max, sum) pairs
-  const int Hp = is_mla(attn) ? (attn.q_heads + 31) / 32 * 32 : attn.q_heads;
+  const int Hp = p.rows ? attn.q_heads : (attn.q_heads + 31) / 32 * 32;
   const size_t o_bytes = (size_t)units * p.n_parts * Hp * attn.d_v * sizeof(float);
   const float* part_o = reinterpret_cast<const float*>(workspace);
   const float2* part_ml = reinterpret_cast<const float2*>(
@@ -1484,7 +1513,7 @@ hipError_t launch_merge(const AttnPlan& p, const hisparse_attn_desc_t& attn, int
   if (prefetch && prefetch->units > 0 && prefetch->n_layers > 0 &&
       !carried_replay(*prefetch, 256, 1 << 20, prefetch_threads, prefetch_block_bytes, &rp))
     return hipErrorInvalidValue;
-  if (is_mla(attn)) {
+  if (!p.rows) {
     const int nb = Hp / 32;
     CombineMlaArgs c{part_o, part_ml, out, attn.q_heads, Hp, p.n_parts, 0, rp};
     if ((int64_t)units * nb * 16 >= 2 * kTargetWorkgroups) {
@@ -1500,7 +1529,10 @@ hipError_t launch_merge(const AttnPlan& p, const hisparse_attn_desc_t& attn, int
   }
   CombineArgs c{part_o, part_ml, out, attn.q_heads, p.n_parts, units * attn.q_heads, 0, rp};
   c.n_wg = (units * attn.q_heads + 3) / 4;
-  hipLaunchKernelGGL(attn_combine_kernel, dim3(c.n_wg + rp.pf_wg), dim3(256), 0, stream, c);
+  if (is_mla(attn))
+    hipLaunchKernelGGL(attn_combine_kernel<512>, dim3(c.n_wg + rp.pf_wg), dim3(256), 0, stream, c);
+  else
+    hipLaunchKernelGGL(attn_combine_kernel<128>, dim3(c.n_wg + rp.pf_wg), dim3(256), 0, stream, c);
   return hipGetLastError();
 }
 

@@ -131,6 +131,7 @@ int resolve_threads(int32_t B);
 struct AttnPlan {
   int32_t hw, tw, hb;        // head waves, token waves, head blocks
   int32_t tg;                // latent attention: token groups merged within a workgroup
+  bool rows;                 // 16 heads per wave, partial results stored row by row
   bool paced;                // latent attention: the query loaded after the first chunks
   int32_t n_tok;             // tokens per unit = k * tokens_per_record
   int32_t split_tokens;      // tokens per workgroup split (multiple of 32 * tw)
