@@ -508,23 +508,28 @@ __global__ __launch_bounds__(kFetchThreads) void fetch_kernel(FetchArgs a, FastD
                                                               TurnDev turn) {
   // The fetch shares its CUs with other streams' kernels (the other micro-batch's attention and
   // merge); its waves issue little but each issue keeps the host link fed, so they go first.
-  __builtin_amdgcn_s_setprio(3);
+  // While it waits for a turn it stays at the default: its polls would otherwise go before the
+  // host reads it waits for.
+  if (!turn.wait_pair) __builtin_amdgcn_s_setprio(3);
   if (turn.signal_pair && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 &&
       threadIdx.x == 0)
     __hip_atomic_fetch_max(turn.signal_pair + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (turn.wait_pair) {
     // Waves of a launch that waits for its turn are resident already and poll its state (an
-    // uncached device-scope read every few hundred cycles), so the link passes from one launch
-    // to the next without a dependency through the command processor.
+    // uncached device-scope read about every 2000 cycles), so the link passes from one launch
+    // to the next without a dependency through the command processor. Polls slow the fetch that
+    // holds the link (they share its CUs' memory pipelines): every 512 cycles, the two-micro-batch
+    // step over 64-token blocks took 1.625 ms, every 2048 1.579, every 8128 1.597.
     const uint64_t t0 = wall_clock64();
     for (;;) {
       const int32_t st =
           __hip_atomic_load(turn.wait_pair + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint64_t dt = wall_clock64() - t0;
       if (st >= 2 || dt >= kTurnWaitTicks || (st == 0 && dt >= kTurnStartTicks)) break;
-      __builtin_amdgcn_s_sleep(8);
+      __builtin_amdgcn_s_sleep(32);
     }
   }
+  __builtin_amdgcn_s_setprio(3);
   // grid z: the target layers (one plan, each layer's own host records and cache)
   fetch_slice<U>(a, div_cpr, blockIdx.y, blockIdx.z,
                  blockIdx.x * (uint32_t)kFetchThreads + threadIdx.x,
