@@ -144,10 +144,11 @@ typedef struct {
  * d_out; hisparse_attention_merge then writes d_out from them. For callers that schedule,
  * overlap or time the two kernels apart. */
 #define HISPARSE_ATTN_DEFER_MERGE 1
-/* hisparse_attn_desc_t.flags, a scheduling hint for latent attention: the call runs beside
+/* hisparse_attn_desc_t.flags, a scheduling hint: the call runs beside
  * another stream's host-link fetch (e.g. two micro-batches taking turns on the link), whose slow
- * host reads occupy the memory pipelines of the CUs they run on. The plan then aims at half a
- * workgroup per CU instead of one (fewer, longer splits): the fetch's waves find CUs without an
+ * host reads occupy the memory pipelines of the CUs they run on. The plan then takes fewer, longer
+ * splits (latent attention: half a workgroup per CU instead of one; grouped-query records: at
+ * least six rounds of a workgroup's waves per split): the fetch's waves find CUs without an
  * attention workgroup, and the split partial results shrink; on a GPU of its own the call is
  * slower that way. Results differ only within rounding (other split boundaries); each plan is
  * deterministic. */

@@ -1382,10 +1382,16 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     splits = std::max(1, target / per_split);
     // A round is one chunk per token group. Latent attention: the split partials and the merge
     // grow with the splits: one round per split up to 4 workgroup columns and from 16 on (where
-    // the grid limits the splits anyway), two between. Grouped-query: two rounds per split; a
-    // round takes about 1 us, and 4 units x 4096 tokens take 10.9 us in 16 splits (two rounds each)
-    // against 11.8 in 8, 16 units x 2048 tokens 10.8 in 8 against 12.4 in 4.
-    int split_rounds = is_mla(*attn) ? 1 : 2;
+    // the grid limits the splits anyway), two between. Grouped-query, four token groups: two
+    // rounds of 128 tokens per split; a round takes about 1 us, and 4 units x 4096 tokens take 10.9
+    // us in 16 splits (two rounds each) against 11.8 in 8, 16 units x 2048 tokens 10.8 in 8 against
+    // 12.4 in 4. With fewer token groups, whose rounds are shorter, four (8 units of 32 heads x
+    // 4096 tokens: 12.4 us in 16 splits, 12.5 in 32).
+    // Beside another stream's host-link fetch, six: fewer workgroups leave its waves their CUs (two
+    // micro-batches of 32 units x 16 heads x 1536 tokens: decode step 1.587 ms with four rounds,
+    // 1.552 with six, 1.561 with twelve; of 32 x 4 x 4096: 6.107, 6.105, 6.128).
+    const bool beside = attn->flags & HISPARSE_ATTN_BESIDE_FETCH;
+    int split_rounds = is_mla(*attn) ? 1 : (beside ? 6 : (p.tw == 4 ? 2 : 4));
     if (is_mla(*attn) && per_split > 4 && per_split < 16) split_rounds = 2;
     // A call that carries a replay lasts as long as the replay's host reads; its attention only
     // has to finish within them, and the merge after it is on the decode chain. One request of
@@ -1417,10 +1423,8 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   const int64_t n_wg = (int64_t)units * p.n_wg_splits * p.hb;
   if (n_wg > (1LL << 30)) return HISPARSE_ERR_INVALID_ARG;
   const int h_store = is_mla(*attn) ? (H + 31) / 32 * 32 : H;
-  // grouped-query sizes count one part per token group, as callers may have stored them
-  const int per_part = is_mla(*attn) ? 1 : p.tw;
-  const size_t o_bytes = (size_t)units * p.n_parts * per_part * h_store * attn->d_v * sizeof(float);
-  const size_t ml_bytes = (size_t)units * p.n_parts * per_part * H * sizeof(float2);
+  const size_t o_bytes = (size_t)units * p.n_parts * h_store * attn->d_v * sizeof(float);
+  const size_t ml_bytes = (size_t)units * p.n_parts * H * sizeof(float2);
   p.workspace_bytes = ((o_bytes + 255) & ~(size_t)255) + ml_bytes;
   *plan = p;
   return HISPARSE_OK;
