@@ -1,0 +1,144 @@
+"""GPU parity at the edges where the kernels change shape: attention's token rounds, head blocks,
+split cap and single-split output against the float64 oracle, and the tables' recency index read
+16 bytes at a time or entry by entry against the canonical LRU.
+
+Attention tolerance: weights rounded to bf16 (relative step 2^-9, one rounding per weight) and
+fp32 sums, as for every attention test here: max-abs 1e-2, relative L2 5e-3.
+"""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workload as W
+from hs_harness import attn_desc, log
+from paper_2608_07009_amd import HiSparseCache, hisparse as hs
+
+pytestmark = pytest.mark.gpu
+
+MAX_ABS, REL_L2 = 1e-2, 5e-3
+BESIDE = hs.HISPARSE_ATTN_BESIDE_FETCH
+DEFER = hs.HISPARSE_ATTN_DEFER_MERGE
+
+
+@pytest.mark.parametrize("kind,H,k,tpr,splits,units,flags", [
+    # latent, one round of four 16-head waves (up to 16 heads, up to 128 tokens) and its far side
+    ("mla", 16, 128, 1, 0, 2, 0), ("mla", 1, 127, 1, 0, 1, 0), ("mla", 15, 31, 4, 0, 3, 0),
+    ("mla", 16, 32, 4, 0, 2, 0), ("mla", 16, 129, 1, 0, 2, 0), ("mla", 17, 128, 1, 0, 2, 0),
+    ("mla", 16, 1, 1, 0, 1, 0), ("mla", 16, 33, 4, 0, 2, 0),
+    # latent, a unit of one split: one head wave, two, and two with the query after the first chunk
+    ("mla", 20, 64, 1, 0, 2, 0), ("mla", 32, 65, 1, 1, 2, 0), ("mla", 33, 63, 1, 0, 2, 0),
+    ("mla", 128, 50, 1, 0, 9, BESIDE), ("mla", 72, 64, 1, 1, 2, 0), ("mla", 128, 200, 1, 0, 9, BESIDE),
+    # latent, both sides of the 2048-record split cap
+    ("mla", 40, 2048, 1, 1, 1, 0), ("mla", 40, 2049, 1, 1, 1, 0), ("mla", 20, 2048, 1, 1, 1, 0),
+    # grouped-query, one to four head waves: one split (five rounds), and one more
+    ("gqa", 4, 640, 1, 0, 2, 0), ("gqa", 4, 641, 1, 0, 2, 0), ("gqa", 16, 40, 16, 0, 2, 0),
+    ("gqa", 17, 320, 1, 0, 2, 0), ("gqa", 32, 321, 1, 0, 2, 0), ("gqa", 33, 160, 1, 0, 2, 0),
+    ("gqa", 64, 161, 1, 0, 2, 0), ("gqa", 70, 3, 64, 0, 2, 0), ("gqa", 5, 1, 1, 0, 2, 0),
+    ("gqa", 8, 2048, 1, 1, 1, 0), ("gqa", 8, 2049, 1, 1, 1, 0),
+])
+def test_attention_shape_edges(kind, H, k, tpr, splits, units, flags):
+    """Against the oracle, with padding entries and (from two units on) a unit with nothing
+    selected; the deferred call and its merge give the same bits as the call by itself."""
+    rng = np.random.default_rng(zlib.crc32(f"edge-{kind}-{H}-{k}-{tpr}-{splits}".encode()))
+    if kind == "mla":
+        d_qk, d_v, voff, te, scale = 576, 512, 0, 576, 1 / np.sqrt(192)
+    else:
+        d_qk, d_v, voff, te, scale = 128, 128, 128, 256, 1 / np.sqrt(128)
+    n_rec, R = k + 19, te * tpr * 2
+    w = W.workload(1 if kind == "mla" else 3, q_heads=H, k=k, d_qk=d_qk, d_v=d_v, v_offset=voff,
+                   tokens_per_record=tpr, record_bytes=R, scale=float(scale))
+    bf16 = lambda shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)) \
+        .to(torch.bfloat16).view(torch.int16)
+    pool, q = bf16((units, n_rec, te * tpr)), bf16((units, H, d_qk))
+    idx = np.stack([rng.choice(n_rec, size=k, replace=False) for _ in range(units)]).astype(np.int32)
+    if k > 4:
+        idx[0, k // 3::7] = -1
+    if units > 1:
+        idx[1, :] = -1
+    log(f"test_attention_shape_edges {kind} H={H} k={k} tpr={tpr} splits={splits} units={units}")
+    dev = torch.device("cuda:0")
+    pool_d, q_d, idx_d = pool.to(dev), q.to(dev), torch.from_numpy(idx).to(dev)
+    ad = attn_desc(w, splits, flags)
+    n = hs.hisparse_decode_workspace_bytes(units, k, R, ad)
+    ws = torch.full((n,), 0xFF, dtype=torch.uint8, device=dev)  # partials never read unwritten
+    s = torch.cuda.current_stream()
+    out = torch.full((units, H, d_v), float("nan"), dtype=torch.float32, device=dev)
+    hs.hisparse_sparse_decode_pool(pool_d, n_rec, R, units, k, q_d, idx_d, out, ad, ws, n, s)
+    late = torch.full_like(out, float("nan"))
+    add = attn_desc(w, splits, flags | DEFER)
+    hs.hisparse_sparse_decode_pool(pool_d, n_rec, R, units, k, q_d, idx_d, late, add, ws, n, s)
+    hs.hisparse_attention_merge(units, k, R, add, late, ws, n, s)
+    o, l = out.cpu().numpy(), late.cpu().numpy()
+    assert o.tobytes() == l.tobytes()
+    for u in range(units):
+        if u == 1:
+            assert (o[u] == 0).all()
+            continue
+        ref = oracle.sparse_decode(q[u].numpy().view(np.uint16), pool[u].numpy().view(np.uint16),
+                                   idx[u], d_qk=d_qk, d_v=d_v, v_off=voff, token_elems=te,
+                                   tokens_per_record=tpr, scale=w.scale)
+        assert np.abs(o[u] - ref).max() <= MAX_ABS
+        assert np.linalg.norm(o[u] - ref) <= REL_L2 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("B,k", [(1, 1), (3, 2), (4, 4), (7, 5), (63, 31), (64, 64), (66, 40),
+                                 (255, 100), (260, 256), (1000, 513), (1023, 700), (4094, 2048),
+                                 (4096, 4096), (4097, 1500), (4100, 2000), (8191, 3000),
+                                 (16384, 4096)])
+def test_tables_recency_index_edges(B, k):
+    """Resolves of drifting selections and one-position admissions in turn, at capacities on both
+    sides of every change in how the recency index is read (16 bytes or one entry at a time, 4 or
+    16 entries per thread, one or several admission batches): slots, counts, state and recency
+    index as the canonical LRU gives them, for three units."""
+    U, G, L = 3, 2, 3 * B + k + 40
+    rng = np.random.default_rng(B * 7 + k)
+    log(f"test_tables_recency_index_edges B={B} k={k}")
+    cache = HiSparseCache(num_requests=U, num_layers=G, units_per_request=1, capacity=B,
+                          num_records=L, top_k=k, record_bytes=48, share_group=G)
+    try:
+        dev = torch.device("cuda:0")
+        for layer in range(G):
+            cache.host_view(layer)[:] = 0
+        slots = torch.empty((U, k), dtype=torch.int32, device=dev)
+        counts = torch.empty((U, 2), dtype=torch.int32, device=dev)
+        new_slots = torch.empty((1, U), dtype=torch.int32, device=dev)
+        orc = oracle.OracleCache(U, L, B, k)
+        s = torch.cuda.current_stream()
+        sel = np.stack([rng.choice(L, size=k, replace=False) for _ in range(U)]).astype(np.int32)
+        for t in range(6):
+            for u in range(U):  # a fifth of the entries change; unit 2 pads its tail
+                fresh = np.setdiff1d(np.arange(L), sel[u])
+                at = rng.choice(k, size=max(1, k // 5), replace=False)
+                sel[u, at] = rng.choice(fresh, size=len(at), replace=False)
+            step = sel.copy()
+            step[2, k - k // 4:] = -1
+            hs.hisparse_resolve(cache.handle, 0, torch.from_numpy(step).to(dev), slots, counts, s)
+            e_slots, e_counts, _, _, bad = orc.resolve(step)
+            assert bad == 0
+            assert (slots.cpu().numpy() == e_slots).all(), f"slots, step {t}"
+            assert (counts.cpu().numpy() == e_counts).all(), f"counts, step {t}"
+            # a resident position, a new one, and none
+            pos = np.array([step[0, 0], rng.integers(L), -1], dtype=np.int32)
+            rec = torch.full((G, U, 24), t + 1, dtype=torch.int16, device=dev)
+            hs.hisparse_append(cache.handle, 0, G, torch.from_numpy(pos).to(dev), rec, new_slots, s)
+            got = new_slots.cpu().numpy()[0]
+            for u in range(2):
+                rc, slot, _ = orc.admit_unit(u, int(pos[u]))
+                assert rc == oracle.OK and got[u] == slot, f"admission, step {t} unit {u}"
+                for layer in range(G):
+                    host = cache.host_view(layer)[u, pos[u]].view(np.int16)
+                    assert (host == t + 1).all(), f"write-through, step {t} unit {u} layer {layer}"
+            assert got[2] == -1
+            orc.clock[2] += 1
+        st = cache.read_state(0)
+        assert (st["slot_pos"] == orc.slot_pos).all() and (st["slot_ts"] == orc.slot_ts).all()
+        assert (st["clock"] == orc.clock).all() and (st["page_table"] == orc.pt).all()
+        order = np.stack([np.lexsort((np.arange(B), ts)) for ts in orc.slot_ts])
+        assert (st["order"] == order).all()
+        assert cache.check_errors()[0] == hs.HISPARSE_OK
+    finally:
+        torch.cuda.synchronize()
+        cache.close()
