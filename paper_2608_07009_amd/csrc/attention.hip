@@ -742,10 +742,17 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 
 // Latent attention (d_qk 576, d_v 512 = the first 512 key dims). One workgroup per
 // (unit, token split, head block of 32 * HW heads); wave w owns 32 heads (w % HW) of token
-// group w / HW. Each token group has its own ring of NST chunk tiles in LDS, staged once for its
-// HW head waves; with TG = 2 groups the split's 32-token chunks alternate between the groups and
-// the two groups' results are merged in LDS at the end, so a workgroup writes one partial result
+// group w / HW. Each of the two token groups has its own ring of two chunk tiles in LDS, staged
+// once for its HW head waves; the split's 32-token chunks alternate between the groups, and the
+// two groups' results are merged in LDS at the end, so a workgroup writes one partial result
 // for twice the tokens of one group (half the partial traffic of two workgroups).
+// Bound: a round (one chunk per group) takes 2.0 us with the GPU to itself, 0.9 of them MFMA
+// issue, 0.35 softmax and the rest waiting for the next chunk, of which LDS holds only one (four
+// tiles of 36 KB fill it). Many workgroups of 16-32 heads reach the HBM rate instead (64 units x
+// 16 heads: 6.3 TB/s in the loop); calls of few rounds are bound by the chain of index, first
+// chunk, result and merge. Measured, merge included, before these tiles -> now: 96 units x 128
+// heads x 2048 tokens 137 -> 87.5 us, 64 x 16 81 -> 40.8, 16 x 128 33.5 -> 28.2 (of which 67 MB of
+// partials written and read are 13), 5 x 72 x 1337 26.0 -> 17.3, 1 x 128 19.0 -> 16.7.
 //   S^T[token][head] = K[token][:] . Q^T[:][head]   v_mfma_f32_32x32x16_bf16, 36 k-steps, K rows
 //                                                   from LDS, Q resident in VGPRs
 //   O[head][dim]    += P[head][token] . V[token][dim]  v_mfma_f32_32x32x16_bf16, 2 k-steps x 16

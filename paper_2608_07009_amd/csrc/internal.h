@@ -134,9 +134,9 @@ struct AttnPlan {
   bool rows;                 // 16 heads per wave, partial results stored row by row
   bool paced;                // latent attention: the query loaded after the first chunks
   int32_t n_tok;             // tokens per unit = k * tokens_per_record
-  int32_t split_tokens;      // tokens per workgroup split (multiple of 32 * tw)
+  int32_t split_tokens;      // tokens per workgroup split (multiple of a round: 32 * tg * tw)
   int32_t n_wg_splits;       // workgroup splits per unit
-  int32_t n_parts;           // partial results per (unit, head) = n_wg_splits * tw
+  int32_t n_parts;           // partial results per (unit, head) = n_wg_splits
   size_t workspace_bytes;
 };
 hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_bytes,
