@@ -7,10 +7,11 @@
 // Structure (every attention kernel: one workgroup per (unit, token split, head block); each
 // 32-token chunk is staged into LDS once with direct global->LDS loads and shared by the
 // workgroup's head waves)
-//   attn_partial_kernel  grouped-query records (d 128), bound by HBM for large calls (64 units x 4
-//     heads x 4096 tokens, 134 MB: 36.3 us with one partial result per wave, 29.6 now, merge
-//     included; the copy rate gives 26) and by latency for small ones. A wave owns 16 query heads (the MFMA N
-//     dimension) and one 32-token chunk per iteration.
+//   attn_partial_kernel  grouped-query records (d 128), and latent calls of up to 16 heads over at
+//     most 128 tokens. Bound by HBM for large calls (64 units x 4 heads x 4096 tokens, 134 MB:
+//     36.3 us with one partial result per wave, 29.7 now, merge included; the copy rate gives 26)
+//     and by latency for small ones. A wave owns 16 query heads (the MFMA N dimension) and one
+//     32-token chunk per iteration.
 //       S^T[token][head] = K[token][:] . Q^T[:][head]     v_mfma_f32_16x16x32_bf16, K from LDS
 //                                                        rows, Q resident in VGPRs
 //       online softmax in fp32 (exp2, reference max per head), P rounded to bf16
@@ -338,9 +339,10 @@ __device__ __forceinline__ void valid_words(uint32_t* s_valid, const int32_t* s_
 }
 
 // The calling wave's loads of the current chunk are done once at most `younger` (at most
-// NST - 2, none with one buffer) later chunks' loads, LPW each, are outstanding; then the workgroup synchronises. With
-// one head wave per token group (HW = 1) the tiles are the wave's own and nobody waits for
-// another wave: the waves drift apart and one's loads overlap another's arithmetic.
+// NST - 2, none with one buffer) later chunks' loads, LPW each, are outstanding; then the
+// workgroup synchronises. With one head wave per token group (HW = 1) the tiles are the wave's
+// own and nobody waits for another wave: the waves drift apart and one's loads overlap another's
+// arithmetic.
 template <int N, bool BARRIER>
 __device__ __forceinline__ void wait_loads() {
   if constexpr (BARRIER) wait_loads_and_barrier<N>();
