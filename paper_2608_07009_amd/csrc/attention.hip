@@ -118,13 +118,42 @@ __device__ __host__ inline int64_t mla_part_offset(int head, int dim) {
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// Two softmax weights 2^(s0 scale - m), 2^(s1 scale - m) rounded to bf16 (nearest even, one
-// packed v_cvt_pk_bf16_f32), the first in the low half. The exponential is the hardware
-// v_exp_f32: weights below 2^-126 flush to zero.
-__device__ inline uint32_t weights_bf16x2(float s0, float s1, float scale, float m) {
-  const f32x2 e = {__builtin_amdgcn_exp2f(__builtin_fmaf(s0, scale, -m)),
-                   __builtin_amdgcn_exp2f(__builtin_fmaf(s1, scale, -m))};
+// Two softmax weights 2^e0, 2^e1 rounded to bf16 (nearest even, one packed v_cvt_pk_bf16_f32), the
+// first in the low half. The exponential is the hardware v_exp_f32: weights below 2^-126 flush to
+// zero.
+__device__ inline uint32_t weights_bf16x2(float e0, float e1) {
+  const f32x2 e = {__builtin_amdgcn_exp2f(e0), __builtin_amdgcn_exp2f(e1)};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(e, bf16x2_t));
+}
+// s * scale - m with the product rounded first, as the products that references are taken from are:
+// 0 for the score that m is.
+__device__ inline float over_reference(float s, float scale, float m) {
+#pragma clang fp contract(off)
+  return s * scale - m;
+}
+// Up to this reference (powers of two) a weight comes from one fused multiply-add: against the
+// rounded product m, the score that m is then weighs 2^0.5 at most, and so do its peers, which the
+// softmax does not see. Beyond 2^31 such a weight would leave the float range; there the product is
+// rounded first (for every score: 96 units of 128 heads x 2048 tokens 88.2 us, this way 87.5).
+constexpr float kFusedReference = 16777216.f;
+// The weights of N scores of one head against its reference m, two to a word.
+template <int N>
+__device__ __forceinline__ void softmax_weights(uint32_t (&pw)[N / 2], const float (&sc)[N],
+                                                float scale, float m) {
+#pragma unroll
+  for (int j = 0; j < N; j += 2)
+    pw[j >> 1] = weights_bf16x2(__builtin_fmaf(sc[j], scale, -m),
+                                __builtin_fmaf(sc[j + 1], scale, -m));
+  // some head of the wave has a larger reference, or none yet and weighs nothing
+  if (__ballot(!(__builtin_fabsf(m) <= kFusedReference))) {
+#pragma unroll
+    for (int j = 0; j < N; j += 2) {
+      const uint32_t rounded = weights_bf16x2(over_reference(sc[j], scale, m),
+                                              over_reference(sc[j + 1], scale, m));
+      pw[j >> 1] = m == -INFINITY ? 0u
+                   : __builtin_fabsf(m) <= kFusedReference ? pw[j >> 1] : rounded;
+    }
+  }
 }
 // sum + both (rounded) weights of w.
 __device__ inline float add_weights(uint32_t w, float sum) {
@@ -466,13 +495,7 @@ void attn_partial_kernel(AttnArgs a) {
   };
   auto finish_chunk = [&](const uint8_t* tile) {
     uint32_t pw[4];
-#pragma unroll
-    for (int j = 0; j < 8; j += 2)
-      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
-    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
-#pragma unroll
-      for (int j = 0; j < 4; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
-    }
+    softmax_weights<8>(pw, sc, a.scale_log2, m_run);
 #pragma unroll
     for (int j = 0; j < 4; ++j) l_run = add_weights(pw[j], l_run);
     const bf16x8_t pa = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});
@@ -717,10 +740,9 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
       for (int i = 0; i < DQK / 64; ++i) d += qv[i] * bf16_to_f32(kt[lane + 64 * i]);
 #pragma unroll
       for (int x = 32; x >= 1; x >>= 1) d += __shfl_xor(d, x, 64);
-      const float sc = d * a.scale_log2;
-      const float m_new = fmaxf(m, sc);
+      const float m_new = fmaxf(m, d * a.scale_log2);
       const float alpha = exp2f(m - m_new);
-      const float pr = exp2f(sc - m_new);
+      const float pr = exp2f(over_reference(d, a.scale_log2, m_new));
       l = l * alpha + pr;
 #pragma unroll
       for (int e = 0; e < DV / 64; ++e)
@@ -922,13 +944,7 @@ void attn_mla_kernel(AttnArgs a) {
     };
     static_for<VD>(vread);  // in flight while the weights are worked out
     uint32_t pw[8];
-#pragma unroll
-    for (int j = 0; j < 16; j += 2)
-      pw[j >> 1] = weights_bf16x2(sc[j], sc[j + 1], a.scale_log2, m_run);
-    if (__ballot(m_run == -INFINITY)) {  // a head without a reference yet weighs nothing
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pw[j] = m_run == -INFINITY ? 0u : pw[j];
-    }
+    softmax_weights<16>(pw, sc, a.scale_log2, m_run);
 #pragma unroll
     for (int j = 0; j < 8; ++j) l_run = add_weights(pw[j], l_run);
     const bf16x8_t pa0 = __builtin_bit_cast(bf16x8_t, u32x4{pw[0], pw[1], pw[2], pw[3]});

@@ -142,3 +142,59 @@ def test_tables_recency_index_edges(B, k):
     finally:
         torch.cuda.synchronize()
         cache.close()
+
+
+def _score_case(kind, H, k, units, rng, key, query):
+    """Inputs whose scores are products of two bf16 numbers, exact in fp32: one key dimension (of
+    latent records one outside the values) holds key [units][k], the query there query [H]."""
+    mla = kind == "mla"
+    d_qk, d_v, voff, te = (576, 512, 0, 576) if mla else (128, 128, 128, 256)
+    R, scale = te * 2, float(1 / np.sqrt(192 if mla else 128))
+    w = W.workload(1 if mla else 3, q_heads=H, k=k, d_qk=d_qk, d_v=d_v, v_offset=voff,
+                   tokens_per_record=1, record_bytes=R, scale=scale)
+    pool = rng.standard_normal((units, k, te)).astype(np.float32)
+    q = np.zeros((units, H, d_qk), np.float32)
+    pool[:, :, d_qk - 1], q[:, :, d_qk - 1] = key, query
+    bf16 = lambda a: torch.from_numpy(a).to(torch.bfloat16).view(torch.int16)
+    idx = np.stack([rng.permutation(k) for _ in range(units)]).astype(np.int32)
+    return w, bf16(pool), bf16(q), idx
+
+
+def _pool_call(w, pool, q, idx, splits, flags, units):
+    dev = torch.device("cuda:0")
+    ad = attn_desc(w, splits, flags)
+    n = hs.hisparse_decode_workspace_bytes(units, w.k, w.record_bytes, ad)
+    ws = torch.full((n,), 0xFF, dtype=torch.uint8, device=dev)
+    out = torch.full((units, w.q_heads, w.d_v), 7.0, dtype=torch.float32, device=dev)
+    hs.hisparse_sparse_decode_pool(pool.to(dev), pool.shape[1], w.record_bytes, units, w.k,
+                                   q.to(dev), torch.from_numpy(idx).to(dev), out, ad, ws, n,
+                                   torch.cuda.current_stream())
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind,H,k,splits,units,flags", [
+    # one chunk per token group: 16-head kernel, one and two head waves written directly, merged,
+    # and with the query after the first chunk
+    ("mla", 16, 128, 0, 2, 0), ("mla", 20, 64, 1, 2, 0), ("mla", 72, 64, 1, 2, 0),
+    ("mla", 40, 128, 2, 1, 0), ("mla", 128, 50, 0, 9, BESIDE),
+    # more chunks: scores outgrow the reference (exact fallback; the moving reference)
+    ("mla", 20, 200, 1, 2, 0), ("gqa", 4, 600, 1, 2, 0), ("gqa", 24, 300, 2, 2, 0),
+    ("gqa", 64, 200, 0, 2, 0),
+])
+def test_attention_huge_scores(kind, H, k, splits, units, flags):
+    """Scores of 2^34 and more (in powers of two), 2^27 and more apart: the softmax is one
+    record. fp32 holds such a score to about 2^10, so a weight taken from an unrounded product
+    against a rounded reference would be 0 or infinite; every value out is that record's, exactly."""
+    rng = np.random.default_rng(zlib.crc32(f"huge-{kind}-{H}-{k}-{splits}".encode()))
+    log(f"test_attention_huge_scores {kind} H={H} k={k} splits={splits} units={units}")
+    # k distinct bf16 numbers, neighbours 2^14 apart or more
+    steps = np.concatenate([np.arange(1, 257), *(np.arange(130, 257, 2) * 2.0 ** e for e in range(7))])
+    key = np.stack([rng.permutation(np.unique(steps)[:k]) for _ in range(units)]) * 2.0 ** 14
+    query = rng.integers(128, 256, H) * 2.0 ** 10 * rng.choice((-1, 1), H)
+    w, pool, q, idx = _score_case(kind, H, k, units, rng, key, query)
+    assert len(np.unique(pool[0, :, w.d_qk - 1])) == k
+    out = _pool_call(w, pool, q, idx, splits, flags, units)
+    v = pool.view(torch.bfloat16).float().numpy()[:, :, w.v_offset:w.v_offset + w.d_v]
+    for u in range(units):
+        best = np.where(query > 0, key[u].argmax(), key[u].argmin())
+        assert (out[u] == v[u, best]).all(), f"unit {u}"
