@@ -274,6 +274,15 @@ template <int P>
 __device__ __forceinline__ void stage_rows(uint8_t* tile, int rg, const uint8_t* src) {
   static_for<Tile<P>::NSEG>([&](auto seg) { stage_block<P, seg>(tile, rg, src); });
 }
+// The same by way of registers, for rows at any address: a direct-to-LDS load has to be aligned.
+template <int P>
+__device__ __forceinline__ void copy_rows(uint8_t* tile, int rg, const uint8_t* src) {
+  typedef u32x4 any_u32x4 __attribute__((aligned(2)));
+  u32x4* dst = reinterpret_cast<u32x4*>(tile + rg * Tile<P>::NSEG * 1024) + (threadIdx.x & 63);
+#pragma unroll
+  for (int seg = 0; seg < Tile<P>::NSEG; ++seg)
+    dst[seg * 64] = *reinterpret_cast<const any_u32x4*>(src + seg * 128);
+}
 // The 16-byte piece (times 16) that a lane fetches for its row of row group rg.
 __device__ inline int stage_piece(int lane, int rg) {
   return ((lane & 7) ^ tile_swizzle(8 * rg + (lane >> 3))) << 4;
@@ -783,7 +792,10 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 //                                                   output tiles, V by LDS transpose reads
 // A lane holds 16 of a head's 32 scores (the other 16 are in lane ^ 32), which are exactly its
 // P operands of the two PV k-steps; O (16 tiles x 16 fp32 per lane) lives in accumulators.
-template <int HW, bool PACED, bool DIRECT>
+// PACED: the query follows the first chunk; DIRECT: a unit is one split, its output is written here;
+// ANYQ: a query that does not start at a multiple of 16 bytes, which direct-to-LDS loads need (a
+// kernel of its own: the branch alone cost the large direct calls up to 0.7%).
+template <int HW, bool PACED, bool DIRECT, bool ANYQ>
 __global__ __launch_bounds__(128 * HW, 1)
 void attn_mla_kernel(AttnArgs a) {
   constexpr int DQK = 576, DV = 512;
@@ -856,10 +868,11 @@ void attn_mla_kernel(AttnArgs a) {
     for (int i = 0; i < 4 / TG; ++i) {
       const int rg = __builtin_amdgcn_readfirstlane(tg) * (4 / TG) + i;
       const int h = head0 + 8 * rg + (lane >> 3);
-      stage_rows<DQK / 8>(q_tile, rg,
-                          reinterpret_cast<const uint8_t*>(
-                              a.q + ((int64_t)unit * a.H + (h < a.H ? h : 0)) * DQK) +
-                              stage_piece(lane, rg));
+      const uint8_t* row = reinterpret_cast<const uint8_t*>(
+                               a.q + ((int64_t)unit * a.H + (h < a.H ? h : 0)) * DQK) +
+                           stage_piece(lane, rg);
+      if constexpr (ANYQ) copy_rows<DQK / 8>(q_tile, rg, row);
+      else stage_rows<DQK / 8>(q_tile, rg, row);
     }
   };
   bf16x8_t qreg[NKK];
@@ -1330,10 +1343,10 @@ void launch_partial(const AttnArgs& args, hipStream_t stream) {
                      dim3(64 * HW * TW), 0, stream, args);
 }
 
-template <int HW, bool PACED = false, bool DIRECT = false>
+template <int HW, bool PACED = false, bool DIRECT = false, bool ANYQ = false>
 void launch_mla(const AttnArgs& args, hipStream_t stream) {
   const int nwg_pad = (args.n_wg + 7) & ~7;
-  hipLaunchKernelGGL((attn_mla_kernel<HW, PACED, DIRECT>), dim3(nwg_pad + args.rp.pf_wg),
+  hipLaunchKernelGGL((attn_mla_kernel<HW, PACED, DIRECT, ANYQ>), dim3(nwg_pad + args.rp.pf_wg),
                      dim3(128 * HW), 0, stream, args);
 }
 
@@ -1506,6 +1519,12 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   if (is_mla(attn) && p.rows) {
     if (p.split_tokens > 4 * kChunk) return hipErrorInvalidValue;  // the plan's: one round
     launch_partial<576, 512, 0, 1, 4, 1>(a, stream);
+  } else if (is_mla(attn) && (reinterpret_cast<uintptr_t>(q) & 15) != 0) {
+    // the same splits and bits, never paced
+    if (p.hw == 1 && direct) launch_mla<1, false, true, true>(a, stream);
+    else if (p.hw == 1) launch_mla<1, false, false, true>(a, stream);
+    else if (direct) launch_mla<2, false, true, true>(a, stream);
+    else launch_mla<2, false, false, true>(a, stream);
   } else if (is_mla(attn)) {
     if (p.hw == 1 && direct) launch_mla<1, false, true>(a, stream);
     else if (p.hw == 1) launch_mla<1>(a, stream);

@@ -198,3 +198,24 @@ def test_attention_huge_scores(kind, H, k, splits, units, flags):
     for u in range(units):
         best = np.where(query > 0, key[u].argmax(), key[u].argmin())
         assert (out[u] == v[u, best]).all(), f"unit {u}"
+
+
+@pytest.mark.parametrize("kind,H,k,splits,units,flags", [
+    ("mla", 16, 100, 0, 1, 0), ("mla", 20, 64, 1, 2, 0), ("mla", 72, 200, 0, 2, 0),
+    ("mla", 128, 50, 0, 9, BESIDE), ("gqa", 24, 300, 2, 2, 0),
+])
+@pytest.mark.parametrize("offset", [1, 4])
+def test_attention_query_at_any_element(kind, H, k, splits, units, flags, offset):
+    """A query that starts 2 or 8 bytes off a 16-byte boundary gives the bits of an aligned one."""
+    rng = np.random.default_rng(zlib.crc32(f"offset-{kind}-{H}-{k}".encode()))
+    log(f"test_attention_query_at_any_element {kind} H={H} k={k} units={units} offset={offset}")
+    key, query = rng.standard_normal((units, k)), rng.standard_normal(H)
+    w, pool, q, idx = _score_case(kind, H, k, units, rng, key, query)
+    q = torch.from_numpy(rng.standard_normal(tuple(q.shape)).astype(np.float32)) \
+        .to(torch.bfloat16).view(torch.int16).to("cuda:0")
+    room = torch.zeros(q.numel() + 8, dtype=torch.int16, device="cuda:0")
+    moved = room[offset:offset + q.numel()].view(q.shape).copy_(q)
+    assert q.data_ptr() % 16 == 0 and moved.data_ptr() % 16 == 2 * offset
+    aligned = _pool_call(w, pool, q, idx, splits, flags, units)
+    assert np.isfinite(aligned).all() and np.abs(aligned).max() > 0
+    assert _pool_call(w, pool, moved, idx, splits, flags, units).tobytes() == aligned.tobytes()
