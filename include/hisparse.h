@@ -384,8 +384,12 @@ hisparse_status_t hisparse_append(hisparse_cache_t cache, int32_t first_layer,
                                   int32_t num_layers, const int32_t* d_pos,
                                   const void* d_records, int32_t* d_slots, void* stream);
 
-/* Bytes of device workspace hisparse_sparse_decode(_pool) needs for `units` units of top_k
- * records each; 0 if the descriptor is invalid. */
+/* Bytes of device workspace for hisparse_sparse_decode(_pool) over `units` units of top_k records
+ * each; 0 if the descriptor is invalid. A workspace of this size serves every call of at most
+ * `units` units with the same top_k, record_bytes and attn: a server that sizes one for its largest
+ * batch needs no other. A scheduling hint (HISPARSE_ATTN_BESIDE_FETCH, _CARRIES_REPLAY) can lower the
+ * size and another num_splits can raise it, so a caller that makes calls with several descriptors
+ * takes the largest of their sizes. */
 size_t hisparse_decode_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
                                        const hisparse_attn_desc_t* attn);
 
@@ -426,8 +430,8 @@ hisparse_status_t hisparse_attention_merge(int32_t units, int32_t top_k, int32_t
  * the split partial results go to a scratch array of HISPARSE_NOALLOC_SCRATCH_BYTES that the
  * library holds on each GPU it runs on until the process ends, and the call allocates nothing.
  * Same arguments, output and bits as hisparse_sparse_decode with a workspace.
- *   - HISPARSE_ERR_UNSUPPORTED if the call needs more scratch than that
- *     (hisparse_decode_workspace_bytes(units, k, R, attn) > HISPARSE_NOALLOC_SCRATCH_BYTES);
+ *   - HISPARSE_ERR_UNSUPPORTED if the call needs more scratch than that (never while
+ *     hisparse_decode_workspace_bytes(units, k, R, attn) <= HISPARSE_NOALLOC_SCRATCH_BYTES);
  *   - HISPARSE_ERR_INVALID_ARG with HISPARSE_ATTN_DEFER_MERGE (the partials have no owner).
  * Every call on one GPU shares that GPU's scratch, from any handle: calls that may overlap on
  * one GPU (other streams, other host threads) race and must be ordered by the caller. */

@@ -806,9 +806,7 @@ hisparse_status_t hisparse_prefetch_layers(hisparse_cache_t c, int32_t anchor_la
 
 size_t hisparse_decode_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
                                        const hisparse_attn_desc_t* attn) {
-  hisparse::AttnPlan p{};
-  if (hisparse::plan_attention(units, top_k, record_bytes, attn, &p) != HISPARSE_OK) return 0;
-  return p.workspace_bytes;
+  return hisparse::attention_workspace_bytes(units, top_k, record_bytes, attn);
 }
 
 hisparse_status_t hisparse_sparse_decode_pool(const void* d_pool, int64_t records_per_unit,

@@ -1354,6 +1354,12 @@ bool is_mla(const hisparse_attn_desc_t& d) {
   return d.d_qk == 576 && d.d_v == 512 && d.v_offset == 0;
 }
 
+// Bytes of `parts` partial results: h_store rows of outputs each, then (max, sum) of H heads.
+size_t partials_bytes(size_t parts, int h_store, int H, int d_v) {
+  const size_t o_bytes = parts * h_store * d_v * sizeof(float);
+  return ((o_bytes + 255) & ~(size_t)255) + parts * H * sizeof(float2);
+}
+
 }  // namespace
 
 hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_bytes,
@@ -1460,12 +1466,47 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   if (is_mla(*attn) && p.n_parts > kMlaMaxParts) return HISPARSE_ERR_UNSUPPORTED;
   const int64_t n_wg = (int64_t)units * p.n_wg_splits * p.hb;
   if (n_wg > (1LL << 30)) return HISPARSE_ERR_INVALID_ARG;
-  const int h_store = is_mla(*attn) ? (H + 31) / 32 * 32 : H;
-  const size_t o_bytes = (size_t)units * p.n_parts * h_store * attn->d_v * sizeof(float);
-  const size_t ml_bytes = (size_t)units * p.n_parts * H * sizeof(float2);
-  p.workspace_bytes = ((o_bytes + 255) & ~(size_t)255) + ml_bytes;
+  p.workspace_bytes = partials_bytes((size_t)units * p.n_parts,
+                                     is_mla(*attn) ? (H + 31) / 32 * 32 : H, H, attn->d_v);
   *plan = p;
   return HISPARSE_OK;
+}
+
+// A size for the call that also serves the smaller ones a caller makes with it. The plan's own need
+// is no such size: it falls where a unit becomes one split (64 units of 128 heads x 2048 tokens take
+// 128 parts, 96 take 96), and a hint lowers it.
+//  - every smaller number of units; above one workgroup column per CU a unit takes the fewest splits
+//    there are, so the needs to look at are those up to that many units and the call's own;
+//  - the needs without a hint, for the numbers of units up to the last one whose plan it leaves
+//    alone. It is left out too unless the call is one it is made for: latent, more than 32 heads, at
+//    least 64 pairs of chunks. Where it does lower the need, a part per 1024 records of each unit
+//    still covers smaller calls without it.
+// Calls are checked against their own need, never against this.
+size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
+                                 const hisparse_attn_desc_t* attn) {
+  AttnPlan p{}, bare{};
+  if (plan_attention(units, top_k, record_bytes, attn, &p) != HISPARSE_OK) return 0;
+  hisparse_attn_desc_t plain = *attn;
+  plain.flags &= ~(HISPARSE_ATTN_BESIDE_FETCH | HISPARSE_ATTN_CARRIES_REPLAY);
+  const int H = attn->q_heads;
+  const int record_tokens = std::min(1024 * attn->tokens_per_record, kMaxSplitTokens);
+  const size_t record_parts = (size_t)((p.n_tok + record_tokens - 1) / record_tokens);
+  const int32_t columns = kTargetWorkgroups / p.hb;
+  size_t bytes = 0;
+  bool without_hint = false;
+  for (int32_t u = units; u >= 1; u = std::min(u - 1, columns)) {
+    if (plan_attention(u, top_k, record_bytes, attn, &p) != HISPARSE_OK ||
+        plan_attention(u, top_k, record_bytes, &plain, &bare) != HISPARSE_OK)
+      continue;
+    const bool hinted = is_mla(*attn) && H > 32 && p.n_parts != bare.n_parts &&
+                        (int64_t)u * p.hb * (p.n_tok / (2 * kChunk)) >= 64;
+    without_hint = without_hint || !hinted;
+    bytes = std::max(bytes, p.workspace_bytes);
+    if (without_hint) bytes = std::max(bytes, bare.workspace_bytes);
+    if (hinted)
+      bytes = std::max(bytes, partials_bytes(u * record_parts, (H + 31) / 32 * 32, H, attn->d_v));
+  }
+  return bytes;
 }
 
 hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,

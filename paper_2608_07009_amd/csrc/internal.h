@@ -137,10 +137,14 @@ struct AttnPlan {
   int32_t split_tokens;      // tokens per workgroup split (multiple of a round: 32 * tg * tw)
   int32_t n_wg_splits;       // workgroup splits per unit
   int32_t n_parts;           // partial results per (unit, head) = n_wg_splits
-  size_t workspace_bytes;
+  size_t workspace_bytes;    // what this call needs
 };
 hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_bytes,
                                  const hisparse_attn_desc_t* attn, AttnPlan* plan);
+// The size to give out for it: at least its need, and that of calls of fewer units (see its
+// definition); 0 if the descriptor is invalid.
+size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
+                                 const hisparse_attn_desc_t* attn);
 // The merge of the per-split partials in `workspace` into out (skipped by launch_attention
 // when attn.flags has HISPARSE_ATTN_DEFER_MERGE).
 hipError_t launch_merge(const AttnPlan& p, const hisparse_attn_desc_t& attn, int32_t units,

@@ -235,3 +235,35 @@ def test_carries_replay_plan_takes_longer_splits(units, splits_plain, splits_car
     assert parts(0) == splits_plain
     assert parts(hs.HISPARSE_ATTN_CARRIES_REPLAY) == splits_carry
     assert parts(hs.HISPARSE_ATTN_CARRIES_REPLAY | hs.HISPARSE_ATTN_DEFER_MERGE) == splits_carry
+
+
+@pytest.mark.parametrize("cfg,H,k,tpr", [
+    (2, 128, 2048, 1), (2, 64, 1028, 2), (2, 17, 2923, 1), (2, 65, 7, 64), (2, 8, 193, 4),
+    (2, 16, 128, 1), (2, 33, 1774, 1), (3, 16, 24, 64), (3, 4, 428, 4), (3, 200, 1071, 4),
+    (4, 4, 256, 16), (3, 17, 1228, 2), (3, 40, 3822, 1), (3, 1, 261, 4)])
+def test_workspace_size_covers_smaller_batches(cfg, H, k, tpr):
+    """A workspace sized for a batch is enough for every smaller one: the size never falls as
+    units are added, with or without a hint. Sizes that a hint lowers (latent records, more than
+    32 heads) still hold one partial result per 1024 records of each unit; no other size depends on
+    the hint (there it is never lower than without)."""
+    w = W.workload(cfg)
+    R = w.token_elems * tpr * 2
+    mla = w.d_qk == 576
+    beside, carry = hs.HISPARSE_ATTN_BESIDE_FETCH, hs.HISPARSE_ATTN_CARRIES_REPLAY
+
+    def sizes(flags):
+        d = hs.AttnDesc(H, w.d_qk, w.d_v, w.v_offset, tpr, 0, w.scale, flags)
+        return [hs.hisparse_decode_workspace_bytes(u, k, R, d) for u in range(1, 320)]
+
+    plain = sizes(0)
+    assert plain[0] > 0 and sorted(plain) == plain
+    for flags in (beside, carry, beside | carry):
+        hinted = sizes(flags)
+        assert sorted(hinted) == hinted
+        if mla and H > 32:
+            tokens = min(1024 * tpr, 8192)
+            part = (H + 31) // 32 * 32 * w.d_v * 4 + H * 8
+            assert all(n >= min(p, u * -(-k * tpr // tokens) * part)
+                       for u, (n, p) in enumerate(zip(hinted, plain), 1))
+        else:
+            assert hinted == plain or all(a >= b for a, b in zip(hinted, plain))

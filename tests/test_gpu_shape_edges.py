@@ -219,3 +219,22 @@ def test_attention_query_at_any_element(kind, H, k, splits, units, flags, offset
     aligned = _pool_call(w, pool, q, idx, splits, flags, units)
     assert np.isfinite(aligned).all() and np.abs(aligned).max() > 0
     assert _pool_call(w, pool, moved, idx, splits, flags, units).tobytes() == aligned.tobytes()
+
+
+@pytest.mark.parametrize("kind,H,k,most,units", [("mla", 65, 448, 3, 2), ("mla", 128, 300, 90, 60),
+                                                 ("gqa", 4, 1712, 95, 47)])
+def test_attention_workspace_of_a_larger_batch(kind, H, k, most, units):
+    """A workspace sized for `most` units serves `units`, whose own need is larger."""
+    rng = np.random.default_rng(zlib.crc32(f"workspace-{kind}-{H}-{k}".encode()))
+    log(f"test_attention_workspace_of_a_larger_batch {kind} H={H} k={k} {most} -> {units}")
+    key, query = rng.standard_normal((units, k)), rng.standard_normal(H)
+    w, pool, q, idx = _score_case(kind, H, k, units, rng, key, query)
+    ad, dev = attn_desc(w), torch.device("cuda:0")
+    n = hs.hisparse_decode_workspace_bytes(most, k, w.record_bytes, ad)
+    ws = torch.full((n + 256,), 0xFF, dtype=torch.uint8, device=dev)
+    out = torch.empty((units, H, w.d_v), dtype=torch.float32, device=dev)
+    hs.hisparse_sparse_decode_pool(pool.to(dev), k, w.record_bytes, units, k, q.to(dev),
+                                   torch.from_numpy(idx).to(dev), out, ad, ws, n,
+                                   torch.cuda.current_stream())
+    assert out.cpu().numpy().tobytes() == _pool_call(w, pool, q, idx, 0, 0, units).tobytes()
+    assert (ws[n:] == 0xFF).all()
