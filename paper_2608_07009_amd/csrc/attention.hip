@@ -1378,16 +1378,20 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // HISPARSE_ATTN_BESIDE_FETCH (another stream's host-link fetch shares the GPU) the same
     // shapes take half as many workgroups (below): the other half of the CUs is left to the
     // fetch's waves.
-    // Up to 16 heads over at most 128 tokens, the grouped-query kernel's shape: 16 heads per wave,
-    // four waves on a chunk each, merged in the workgroup, no merge launch: 10.1 us against 11.8
-    // (1 unit) and 10.8 against 13.1 (64 units). Beyond one round it loses what it saves: its
-    // tiles leave no room for the next chunk (256 tokens 12.2 against 11.5 in four splits, 64
-    // units x 2048 tokens 44.9 against 40.8).
-    p.rows = H <= 16 && p.n_tok <= 4 * kChunk;
-    p.hw = H <= 32 ? 1 : 2;
+    // At most 128 tokens, the grouped-query kernel's shape: 16 heads per workgroup, four waves on a
+    // chunk each, merged in the workgroup, no merge launch. One round is all it does well: its
+    // tiles leave no room for the next chunk (16 heads, 256 tokens 12.2 us against 11.5 in four
+    // splits, 64 units x 2048 tokens 44.9 against 40.8). Up to one workgroup per CU it takes 9.2 to
+    // 10.7 us for any number of heads, the tiled kernel 9.7 to 23.7 (1 unit of 128 heads x 128 tokens
+    // 9.2 against 11.8, 32 units 10.6 against 23.7). Beyond that its workgroups, which hold a CU's LDS
+    // each for 16 heads, queue: 48 units of 128 heads x 64 tokens 19.3 against 13.7. With up to 16 heads
+    // the tiled kernel has as many workgroups (300 units x 96 tokens 20.1 against 24.3).
+    p.rows = p.n_tok <= 4 * kChunk &&
+             (H <= 16 || (int64_t)units * ((H + 15) / 16) <= kTargetWorkgroups);
+    p.hw = H <= 32 || p.rows ? 1 : 2;
     p.tg = p.rows ? 1 : 2;
     p.tw = p.rows ? 4 : 1;
-    p.hb = (H + 32 * p.hw - 1) / (32 * p.hw);
+    p.hb = p.rows ? (H + 15) / 16 : (H + 32 * p.hw - 1) / (32 * p.hw);
   } else {              // up to 64 heads per workgroup, 16 per wave
     p.hw = H > 32 ? 4 : (H > 16 ? 2 : 1);
     p.tw = 4 / p.hw;
@@ -1426,31 +1430,43 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     splits = std::max(1, target / per_split);
     // A round is one chunk per token group. Latent attention: the split partials and the merge
     // grow with the splits: one round per split up to 4 workgroup columns and from 16 on (where
-    // the grid limits the splits anyway), two between. Grouped-query, four token groups: two
-    // rounds of 128 tokens per split; a round takes about 1 us, and 4 units x 4096 tokens take 10.9
-    // us in 16 splits (two rounds each) against 11.8 in 8, 16 units x 2048 tokens 10.8 in 8 against
-    // 12.4 in 4. With fewer token groups, whose rounds are shorter, four (8 units of 32 heads x
-    // 4096 tokens: 12.4 us in 16 splits, 12.5 in 32).
+    // the grid limits the splits anyway), two between unless there are at most four in all (8 units
+    // of 32 heads x 192 tokens: 12.1 us in three splits, 16.3 in one). Grouped-query, four token
+    // groups: two rounds of 128 tokens per split; a round takes about 1 us, and 4 units x 4096 tokens
+    // take 10.9 us in 16 splits (two rounds each) against 11.8 in 8, 16 units x 2048 tokens 10.8 in 8
+    // against 12.4 in 4. With fewer token groups, whose rounds are shorter, four (8 units of 32 heads
+    // x 4096 tokens: 12.4 us in 16 splits, 12.5 in 32).
     // Beside another stream's host-link fetch, six: fewer workgroups leave its waves their CUs (two
     // micro-batches of 32 units x 16 heads x 1536 tokens: decode step 1.587 ms with four rounds,
     // 1.552 with six, 1.561 with twelve; of 32 x 4 x 4096: 6.107, 6.105, 6.128).
     const bool beside = attn->flags & HISPARSE_ATTN_BESIDE_FETCH;
     int split_rounds = is_mla(*attn) ? 1 : (beside ? 6 : (p.tw == 4 ? 2 : 4));
-    if (is_mla(*attn) && per_split > 4 && per_split < 16) split_rounds = 2;
+    const int rounds = (p.n_tok + chunk - 1) / chunk;
+    const bool few_columns = is_mla(*attn) && per_split < 16;
+    if (few_columns && per_split > 4 && rounds > 4) split_rounds = 2;
     // A call that carries a replay lasts as long as the replay's host reads; its attention only
     // has to finish within them, and the merge after it is on the decode chain. One request of
     // 128 heads with a replay of its 2048 selections into the next shared layer: 16 four-chunk
     // splits instead of 32 two-chunk ones take the launch from 28.0 to 27.4 us and its merge
     // from 5.8 to 4.6 us (one 1M-token request, 56 layers in groups of 4: decode step 2.299 ->
-    // 2.226 ms), although that attention alone takes longer.
-    if (is_mla(*attn) && per_split < 16 && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
+    // 2.226 ms), although that attention alone takes longer. Not with fewer than 64 one-round
+    // workgroups: their merge is short anyway (2 units of 33 heads x 256 tokens, call and merge: 12.0
+    // against 13.6 us).
+    if (few_columns && per_split * (p.n_tok / chunk) >= 64 &&
+        (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
       split_rounds = 2;
-    const int min_work_splits = std::max(1, p.n_tok / (split_rounds * chunk));
+    // Whole splits of that many rounds at least. A short call takes one more for what is left over
+    // instead of longer ones (5 units of 32 heads x 320 tokens, two rounds per split: 14.0 us in three, 16.1
+    // in two of three rounds); in longer calls, and in those that fill the grid, it is not worth its partials
+    // (4 units of 64 heads x 900 tokens: 15.8 us in 8 splits, 17.4 in 15).
+    const int min_work_splits = few_columns && rounds <= 8
+                                    ? (rounds + split_rounds - 1) / split_rounds
+                                    : std::max(1, p.n_tok / (split_rounds * chunk));
     splits = std::max(1, std::min({splits, max_splits, min_work_splits}));
     // A grouped-query unit of one split needs no merge, a launch of its own that costs about 2.5
     // us, against about 1 us for a round: 11 units x 501 tokens, four rounds, take 8.7 us in one
-    // split against 10.8 in two to four. (A latent round takes 2.1 us: one request of 16 heads
-    // over 128 tokens is no faster in one split of two rounds than in two and a merge.)
+    // split against 10.8 in two to four. (A latent round takes 2 us: one request of 33 heads over
+    // 150 tokens takes 11.7 us in three splits of one round and a merge, 13.9 in one of three.)
     if (!is_mla(*attn) && max_splits <= 5) splits = 1;
   }
   const int max_split_tokens = std::min(kMaxSplitRecords * attn->tokens_per_record, kMaxSplitTokens);
@@ -1478,9 +1494,9 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
 //  - every smaller number of units; above one workgroup column per CU a unit takes the fewest splits
 //    there are, so the needs to look at are those up to that many units and the call's own;
 //  - the needs without a hint, for the numbers of units up to the last one whose plan it leaves
-//    alone. It is left out too unless the call is one it is made for: latent, more than 32 heads, at
-//    least 64 pairs of chunks. Where it does lower the need, a part per 1024 records of each unit
-//    still covers smaller calls without it.
+//    alone; for all of them unless the call is one it is made for: latent, more than 32 heads. Where
+//    it does lower the need, a part per 1024 records of each unit still covers smaller calls
+//    without it.
 // Calls are checked against their own need, never against this.
 size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
                                  const hisparse_attn_desc_t* attn) {
@@ -1498,8 +1514,7 @@ size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_by
     if (plan_attention(u, top_k, record_bytes, attn, &p) != HISPARSE_OK ||
         plan_attention(u, top_k, record_bytes, &plain, &bare) != HISPARSE_OK)
       continue;
-    const bool hinted = is_mla(*attn) && H > 32 && p.n_parts != bare.n_parts &&
-                        (int64_t)u * p.hb * (p.n_tok / (2 * kChunk)) >= 64;
+    const bool hinted = is_mla(*attn) && H > 32 && p.n_parts != bare.n_parts;
     without_hint = without_hint || !hinted;
     bytes = std::max(bytes, p.workspace_bytes);
     if (without_hint) bytes = std::max(bytes, bare.workspace_bytes);

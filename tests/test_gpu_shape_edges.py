@@ -20,17 +20,27 @@ pytestmark = pytest.mark.gpu
 
 MAX_ABS, REL_L2 = 1e-2, 5e-3
 BESIDE = hs.HISPARSE_ATTN_BESIDE_FETCH
+CARRY = hs.HISPARSE_ATTN_CARRIES_REPLAY
 DEFER = hs.HISPARSE_ATTN_DEFER_MERGE
 
 
 @pytest.mark.parametrize("kind,H,k,tpr,splits,units,flags", [
-    # latent, one round of four 16-head waves (up to 16 heads, up to 128 tokens) and its far side
+    # latent, one round of four 16-head waves (up to 128 tokens) and its far side, one to 16 head
+    # blocks, and more of them than CUs (the tiled kernels, in one split and in two)
     ("mla", 16, 128, 1, 0, 2, 0), ("mla", 1, 127, 1, 0, 1, 0), ("mla", 15, 31, 4, 0, 3, 0),
     ("mla", 16, 32, 4, 0, 2, 0), ("mla", 16, 129, 1, 0, 2, 0), ("mla", 17, 128, 1, 0, 2, 0),
     ("mla", 16, 1, 1, 0, 1, 0), ("mla", 16, 33, 4, 0, 2, 0),
-    # latent, a unit of one split: one head wave, two, and two with the query after the first chunk
     ("mla", 20, 64, 1, 0, 2, 0), ("mla", 32, 65, 1, 1, 2, 0), ("mla", 33, 63, 1, 0, 2, 0),
-    ("mla", 128, 50, 1, 0, 9, BESIDE), ("mla", 72, 64, 1, 1, 2, 0), ("mla", 128, 200, 1, 0, 9, BESIDE),
+    ("mla", 128, 50, 1, 0, 9, BESIDE), ("mla", 72, 64, 1, 1, 2, 0), ("mla", 256, 128, 1, 0, 2, 0),
+    ("mla", 241, 32, 4, 0, 16, 0), ("mla", 241, 64, 1, 0, 17, 0), ("mla", 241, 128, 1, 0, 17, 0),
+    # latent, a unit of one split: one head wave, two, and two with the query after the first chunk;
+    # the same kernels with splits to merge
+    ("mla", 20, 129, 1, 1, 2, 0), ("mla", 32, 193, 1, 1, 2, 0), ("mla", 33, 150, 1, 1, 2, 0),
+    ("mla", 72, 192, 1, 1, 2, 0), ("mla", 128, 140, 1, 1, 9, BESIDE), ("mla", 128, 200, 1, 0, 9, BESIDE),
+    # latent, both sides of four rounds and of eight below 16 workgroup columns, with the replay hint
+    ("mla", 32, 256, 1, 0, 5, 0), ("mla", 32, 257, 1, 0, 5, 0), ("mla", 32, 512, 1, 0, 5, 0),
+    ("mla", 32, 513, 1, 0, 5, 0), ("mla", 72, 200, 1, 0, 2, 0), ("mla", 100, 1030, 1, 0, 2, CARRY),
+    ("mla", 100, 900, 1, 0, 2, CARRY),
     # latent, both sides of the 2048-record split cap
     ("mla", 40, 2048, 1, 1, 1, 0), ("mla", 40, 2049, 1, 1, 1, 0), ("mla", 20, 2048, 1, 1, 1, 0),
     # grouped-query, one to four head waves: one split (five rounds), and one more
@@ -172,27 +182,37 @@ def _pool_call(w, pool, q, idx, splits, flags, units):
     return out.cpu().numpy()
 
 
-@pytest.mark.parametrize("kind,H,k,splits,units,flags", [
-    # one chunk per token group: 16-head kernel, one and two head waves written directly, merged,
-    # and with the query after the first chunk
-    ("mla", 16, 128, 0, 2, 0), ("mla", 20, 64, 1, 2, 0), ("mla", 72, 64, 1, 2, 0),
-    ("mla", 40, 128, 2, 1, 0), ("mla", 128, 50, 0, 9, BESIDE),
-    # more chunks: scores outgrow the reference (exact fallback; the moving reference)
-    ("mla", 20, 200, 1, 2, 0), ("gqa", 4, 600, 1, 2, 0), ("gqa", 24, 300, 2, 2, 0),
-    ("gqa", 64, 200, 0, 2, 0),
+@pytest.mark.parametrize("kind,H,k,splits,units,flags,level", [
+    # no later chunk beats its token group's first: 16-head kernel, one and two head waves written
+    # directly, merged, and with the query after the first chunk
+    ("mla", 16, 128, 0, 2, 0, True), ("mla", 100, 128, 0, 2, 0, True), ("mla", 20, 200, 1, 2, 0, True),
+    ("mla", 72, 200, 1, 2, 0, True), ("mla", 24, 300, 2, 2, 0, True), ("mla", 72, 300, 2, 2, 0, True),
+    ("mla", 128, 140, 1, 9, BESIDE, True), ("mla", 128, 270, 2, 9, BESIDE, True),
+    # scores outgrow the reference (exact fallback; the moving reference)
+    ("mla", 20, 200, 1, 2, 0, False), ("mla", 72, 300, 2, 2, 0, False), ("gqa", 4, 600, 1, 2, 0, False),
+    ("gqa", 24, 300, 2, 2, 0, False), ("gqa", 64, 200, 0, 2, 0, False),
 ])
-def test_attention_huge_scores(kind, H, k, splits, units, flags):
+def test_attention_huge_scores(kind, H, k, splits, units, flags, level):
     """Scores of 2^34 and more (in powers of two), 2^27 and more apart: the softmax is one
     record. fp32 holds such a score to about 2^10, so a weight taken from an unrounded product
     against a rounded reference would be 0 or infinite; every value out is that record's, exactly."""
     rng = np.random.default_rng(zlib.crc32(f"huge-{kind}-{H}-{k}-{splits}".encode()))
-    log(f"test_attention_huge_scores {kind} H={H} k={k} splits={splits} units={units}")
+    log(f"test_attention_huge_scores {kind} H={H} k={k} splits={splits} units={units} level={level}")
     # k distinct bf16 numbers, neighbours 2^14 apart or more
     steps = np.concatenate([np.arange(1, 257), *(np.arange(130, 257, 2) * 2.0 ** e for e in range(7))])
     key = np.stack([rng.permutation(np.unique(steps)[:k]) for _ in range(units)]) * 2.0 ** 14
     query = rng.integers(128, 256, H) * 2.0 ** 10 * rng.choice((-1, 1), H)
     w, pool, q, idx = _score_case(kind, H, k, units, rng, key, query)
     assert len(np.unique(pool[0, :, w.d_qk - 1])) == k
+    if level:  # each group's extreme records first: its chunks are every other 32 of its split
+        split = -(-(-(-k // max(splits, 1))) // 64) * 64
+        for u in range(units):
+            for tokens in (np.arange(k)[(np.arange(k) // split == s) & (np.arange(k) // 32 % 2 == g)]
+                           for s in range(-(-k // split)) for g in (0, 1)):
+                for place, extreme in enumerate((np.argmax, np.argmin)[:len(tokens)]):
+                    rest = tokens[place:]
+                    at = rest[extreme(key[u, idx[u, rest]])]
+                    idx[u, [rest[0], at]] = idx[u, [at, rest[0]]]
     out = _pool_call(w, pool, q, idx, splits, flags, units)
     v = pool.view(torch.bfloat16).float().numpy()[:, :, w.v_offset:w.v_offset + w.d_v]
     for u in range(units):
@@ -201,8 +221,9 @@ def test_attention_huge_scores(kind, H, k, splits, units, flags):
 
 
 @pytest.mark.parametrize("kind,H,k,splits,units,flags", [
-    ("mla", 16, 100, 0, 1, 0), ("mla", 20, 64, 1, 2, 0), ("mla", 72, 200, 0, 2, 0),
-    ("mla", 128, 50, 0, 9, BESIDE), ("gqa", 24, 300, 2, 2, 0),
+    ("mla", 16, 100, 0, 1, 0), ("mla", 20, 150, 1, 2, 0), ("mla", 24, 300, 0, 2, 0),
+    ("mla", 72, 200, 0, 2, 0), ("mla", 72, 150, 1, 2, 0), ("mla", 128, 140, 1, 9, BESIDE),
+    ("gqa", 24, 300, 2, 2, 0),
 ])
 @pytest.mark.parametrize("offset", [1, 4])
 def test_attention_query_at_any_element(kind, H, k, splits, units, flags, offset):
