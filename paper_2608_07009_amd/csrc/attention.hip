@@ -1469,7 +1469,15 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // 150 tokens takes 11.7 us in three splits of one round and a merge, 13.9 in one of three.)
     if (!is_mla(*attn) && max_splits <= 5) splits = 1;
   }
-  const int max_split_tokens = std::min(kMaxSplitRecords * attn->tokens_per_record, kMaxSplitTokens);
+  // Splits asked for by number hold 1024 records at most as long as there is a CU for each of the
+  // workgroups that makes: shorter ones are faster there (16 units of 64 heads x 4096 tokens, one
+  // split asked for: 42.4 us in four, 69.7 in two), not beyond (48 units of 128 heads x 4096 tokens,
+  // two asked for: 88.5 us in two, 105.7 in four).
+  const int64_t short_wgs = (int64_t)units * p.hb * ((top_k + kMaxSplitRecords / 2 - 1) /
+                                                     (kMaxSplitRecords / 2));
+  const int max_split_records = attn->num_splits > 0 && short_wgs <= kTargetWorkgroups
+                                    ? kMaxSplitRecords / 2 : kMaxSplitRecords;
+  const int max_split_tokens = std::min(max_split_records * attn->tokens_per_record, kMaxSplitTokens);
   splits = std::max(splits, (p.n_tok + max_split_tokens - 1) / max_split_tokens);
   if (is_mla(*attn)) splits = std::min(splits, kMlaMaxParts);  // the merge keeps weights in LDS
   const int per = (p.n_tok + splits - 1) / splits;

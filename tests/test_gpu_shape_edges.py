@@ -41,13 +41,17 @@ DEFER = hs.HISPARSE_ATTN_DEFER_MERGE
     ("mla", 32, 256, 1, 0, 5, 0), ("mla", 32, 257, 1, 0, 5, 0), ("mla", 32, 512, 1, 0, 5, 0),
     ("mla", 32, 513, 1, 0, 5, 0), ("mla", 72, 200, 1, 0, 2, 0), ("mla", 100, 1030, 1, 0, 2, CARRY),
     ("mla", 100, 900, 1, 0, 2, CARRY),
-    # latent, both sides of the 2048-record split cap
+    # latent, both sides of the 2048-record split cap, and of the 1024-record one of few columns
+    ("mla", 256, 2048, 1, 0, 33, 0), ("mla", 256, 2049, 1, 0, 33, 0), ("mla", 20, 2048, 1, 1, 129, 0),
+    ("mla", 20, 2049, 1, 0, 129, 0),
     ("mla", 40, 2048, 1, 1, 1, 0), ("mla", 40, 2049, 1, 1, 1, 0), ("mla", 20, 2048, 1, 1, 1, 0),
+    ("mla", 72, 1024, 1, 1, 2, 0), ("mla", 20, 1025, 1, 1, 2, 0),
     # grouped-query, one to four head waves: one split (five rounds), and one more
     ("gqa", 4, 640, 1, 0, 2, 0), ("gqa", 4, 641, 1, 0, 2, 0), ("gqa", 16, 40, 16, 0, 2, 0),
     ("gqa", 17, 320, 1, 0, 2, 0), ("gqa", 32, 321, 1, 0, 2, 0), ("gqa", 33, 160, 1, 0, 2, 0),
     ("gqa", 64, 161, 1, 0, 2, 0), ("gqa", 70, 3, 64, 0, 2, 0), ("gqa", 5, 1, 1, 0, 2, 0),
-    ("gqa", 8, 2048, 1, 1, 1, 0), ("gqa", 8, 2049, 1, 1, 1, 0),
+    ("gqa", 8, 2048, 1, 1, 1, 0), ("gqa", 8, 2049, 1, 1, 1, 0), ("gqa", 8, 1024, 1, 1, 1, 0),
+    ("gqa", 256, 2048, 1, 0, 65, 0), ("gqa", 256, 2049, 1, 0, 65, 0),
 ])
 def test_attention_shape_edges(kind, H, k, tpr, splits, units, flags):
     """Against the oracle, with padding entries and (from two units on) a unit with nothing
@@ -57,13 +61,14 @@ def test_attention_shape_edges(kind, H, k, tpr, splits, units, flags):
         d_qk, d_v, voff, te, scale = 576, 512, 0, 576, 1 / np.sqrt(192)
     else:
         d_qk, d_v, voff, te, scale = 128, 128, 128, 256, 1 / np.sqrt(128)
-    n_rec, R = k + 19, te * tpr * 2
+    many = units > 20  # a small pool, records repeated; three of the units against the oracle
+    n_rec, R = 300 if many else k + 19, te * tpr * 2
     w = W.workload(1 if kind == "mla" else 3, q_heads=H, k=k, d_qk=d_qk, d_v=d_v, v_offset=voff,
                    tokens_per_record=tpr, record_bytes=R, scale=float(scale))
     bf16 = lambda shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)) \
         .to(torch.bfloat16).view(torch.int16)
     pool, q = bf16((units, n_rec, te * tpr)), bf16((units, H, d_qk))
-    idx = np.stack([rng.choice(n_rec, size=k, replace=False) for _ in range(units)]).astype(np.int32)
+    idx = np.stack([rng.choice(n_rec, size=k, replace=many) for _ in range(units)]).astype(np.int32)
     if k > 4:
         idx[0, k // 3::7] = -1
     if units > 1:
@@ -83,7 +88,7 @@ def test_attention_shape_edges(kind, H, k, tpr, splits, units, flags):
     hs.hisparse_attention_merge(units, k, R, add, late, ws, n, s)
     o, l = out.cpu().numpy(), late.cpu().numpy()
     assert o.tobytes() == l.tobytes()
-    for u in range(units):
+    for u in (0, 1, units - 1) if many else range(units):
         if u == 1:
             assert (o[u] == 0).all()
             continue
