@@ -581,13 +581,16 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
 // Then the unit's record of each of the group's layers is stored into that slot of the layer's
 // cache and at pos in the layer's host pool. The index is staged in LDS for the shift.
 // Bound: latency. The index entries, and the first record pieces, are read while the position's
-// page-table entry is on its way, sixteen index loads per thread at a time (one after the other,
-// an index of 4096 slots took 7 of the call's 10.9 us).
+// page-table entry is on its way, UN index loads per thread at a time (one after the other, an index
+// of 4096 slots took 7 of the call's 10.9 us). UN is no larger than the index needs: the code runs
+// once per launch, and 16 unrolled loads for an index of up to 256 or 1024 slots cost 0.5 us of
+// instruction fetches (64 units, 128 slots, 1152-byte records: 4.8 us with 16, 4.3 with 1).
+template <int UN>
 __global__ __launch_bounds__(256) void admit_kernel(AdmitArgs a) {
   extern __shared__ uint16_t s_order[];  // [B] (slots < kMaxCapacity = 2^14)
   __shared__ int s_idx;
   typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-  constexpr int NT = 256, UN = 16;
+  constexpr int NT = 256;
   const int unit = blockIdx.x, grp = blockIdx.y, tid = threadIdx.x, B = a.B;
   const int anchor = a.first + grp * a.G;
   const AnchorState st = a.states[anchor / a.G];
@@ -784,8 +787,8 @@ hipError_t launch_turns_reset(int32_t* turns, int32_t n_turns, hipStream_t strea
 
 hipError_t launch_admit(const AdmitArgs& a, int32_t n_groups, hipStream_t stream) {
   static_assert(kMaxCapacity <= 65536, "16-bit slots in the admission kernel's LDS");
-  hipLaunchKernelGGL(admit_kernel, dim3(a.units, n_groups), dim3(256), (size_t)a.B * 2, stream,
-                     a);
+  auto kernel = a.B <= 256 ? admit_kernel<1> : a.B <= 1024 ? admit_kernel<4> : admit_kernel<16>;
+  hipLaunchKernelGGL(kernel, dim3(a.units, n_groups), dim3(256), (size_t)a.B * 2, stream, a);
   return hipGetLastError();
 }
 

@@ -100,7 +100,8 @@ def test_attention_shape_edges(kind, H, k, tpr, splits, units, flags):
 
 
 @pytest.mark.parametrize("B,k", [(1, 1), (3, 2), (4, 4), (7, 5), (63, 31), (64, 64), (66, 40),
-                                 (255, 100), (260, 256), (1000, 513), (1023, 700), (4094, 2048),
+                                 (255, 100), (256, 128), (257, 60), (260, 256), (1000, 513),
+                                 (1023, 700), (1024, 512), (1025, 300), (4094, 2048),
                                  (4096, 4096), (4097, 1500), (4100, 2000), (8191, 3000),
                                  (16384, 4096)])
 def test_tables_recency_index_edges(B, k):
