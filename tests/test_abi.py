@@ -219,10 +219,10 @@ def test_beside_fetch_plan_takes_half_the_workgroups(units, splits_own, splits_b
 @pytest.mark.parametrize("units,splits_plain,splits_carry", [(1, 32, 16), (2, 32, 16), (4, 16, 16),
                                                             (16, 8, 8)])
 def test_carries_replay_plan_takes_longer_splits(units, splits_plain, splits_carry):
-    """The carries-replay hint gives latent attention with one token group per workgroup (fewer
-    than 16 workgroup columns) splits of at least 4 chunks of 32 tokens: for one or two units of
-    128 heads at k = 2048 half the splits (and split partials); from 4 units on the plan already
-    takes 4-chunk splits, and with two token groups (16 units) the hint changes nothing."""
+    """The carries-replay hint gives latent attention of fewer than 16 workgroup columns (64 heads
+    of a unit each) splits of at least two rounds (4 chunks of 32 tokens): for one or two units of
+    128 heads at k = 2048 half the splits (and split partials). The plan for 4 units takes such
+    splits by itself, and from 16 columns on the hint changes nothing."""
     w = W.workload(2)
 
     def parts(flags):

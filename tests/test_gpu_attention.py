@@ -60,11 +60,11 @@ BESIDE = hs.HISPARSE_ATTN_BESIDE_FETCH
 CARRY = hs.HISPARSE_ATTN_CARRIES_REPLAY
 
 
-@pytest.mark.parametrize("cfg,flags", [(1, 0), (2, 0), (2, BESIDE), (3, 0), (4, 0), (5, 0),
-                                       (5, BESIDE), (5, CARRY)])
+@pytest.mark.parametrize("cfg,flags", [(1, 0), (2, 0), (2, BESIDE), (3, 0), (3, BESIDE), (4, 0),
+                                       (4, BESIDE), (5, 0), (5, BESIDE), (5, CARRY)])
 def test_attention_cache_vs_resident_vs_oracle(cfg, flags):
-    """Every latent-attention plan: the default, the beside-fetch hint's (half the workgroups,
-    longer splits) and, for one request, the carries-replay hint's (4-chunk splits)."""
+    """The default plan, the beside-fetch hint's (latent: half the workgroups; grouped-query: six
+    rounds per split) and, for one request, the carries-replay hint's (4-chunk splits)."""
     steps = STEPS[cfg]
     w = W.fit_pinned(W.workload(cfg))
     layer = w.anchors[-1]
@@ -107,7 +107,7 @@ def _bf16(rng, shape):
 @pytest.mark.parametrize("kind,H,k,tpr,splits,units", [
     ("mla", 16, 37, 1, 0, 3), ("mla", 128, 77, 1, 3, 3), ("mla", 40, 300, 1, 0, 3),
     ("mla", 1, 5, 1, 0, 3),
-    # 16 or more workgroup columns: latent attention with two token groups per workgroup
+    # latent, 16 or more workgroup columns
     ("mla", 128, 301, 1, 0, 8), ("mla", 200, 97, 1, 3, 6), ("mla", 128, 64, 1, 0, 9),
     ("gqa", 4, 9, 16, 0, 3), ("gqa", 16, 3, 64, 2, 3), ("gqa", 24, 50, 1, 0, 3),
     ("gqa", 64, 13, 4, 1, 3),
@@ -153,14 +153,17 @@ def test_attention_ragged_and_padding(kind, H, k, tpr, splits, units):
     assert out.tobytes() == out_p.tobytes()
 
 
-@pytest.mark.parametrize("kind,H,splits,units", [("mla", 128, 1, 2), ("mla", 20, 2, 2),
-                                                 ("mla", 128, 1, 8), ("gqa", 16, 1, 2),
-                                                 ("gqa", 64, 0, 2)])
-def test_attention_wide_score_range(kind, H, splits, units):
+@pytest.mark.parametrize("kind,H,splits,units,flags", [
+    # latent, the exact fallback's partial results and outputs: two head waves per token group, one,
+    # and two with the query after the first chunk (more than 16 workgroup columns beside a fetch)
+    ("mla", 128, 1, 2, 0), ("mla", 128, 2, 2, 0), ("mla", 20, 2, 2, 0), ("mla", 20, 1, 2, 0),
+    ("mla", 128, 1, 8, 0), ("mla", 128, 1, 9, BESIDE), ("mla", 128, 2, 9, BESIDE),
+    ("gqa", 16, 1, 2, 0), ("gqa", 64, 0, 2, 0), ("gqa", 64, 0, 2, BESIDE),
+])
+def test_attention_wide_score_range(kind, H, splits, units, flags):
     """Scores that keep growing along the selection (by far more than the kernels' reference
-    slack within one split) exercise the rescale / exact-fallback paths (for latent attention
-    with one and with two token groups per workgroup): still within the oracle's tolerance,
-    still independent of placement."""
+    slack within one split) exercise the rescale / exact-fallback paths: still within the oracle's
+    tolerance, still independent of placement."""
     rng = np.random.default_rng(zlib.crc32(f"wide-{kind}-{H}-{splits}".encode()))
     if kind == "mla":
         d_qk, d_v, voff, te, scale, tpr, k = 576, 512, 0, 576, 1 / np.sqrt(192), 1, 256
@@ -177,7 +180,7 @@ def test_attention_wide_score_range(kind, H, splits, units):
     q_f[:, :, growth] = 1.0
     idx = np.stack([rng.choice(n_rec, size=k, replace=False) for _ in range(units)]).astype(np.int32)
     n_tok = k * tpr
-    rate = 40.0 if kind == "mla" else 25.0
+    rate = 60.0 if kind == "mla" else 25.0
     for u in range(units):
         for i in range(k):
             t = i * tpr + np.arange(tpr)                    # selection-order token numbers
@@ -192,13 +195,19 @@ def test_attention_wide_score_range(kind, H, splits, units):
     sc = np.stack([np.einsum("hd,itd->hit", widen(q[u]), keys[u][idx[u]]).reshape(H, n_tok)
                    for u in range(units)]) * (scale * np.log2(np.e))
     if kind == "mla":
-        # latent kernel: explicit splits of whole 32-token chunks, reference = the max of the
-        # split's first chunk; a score more than 64 above it sends the split to the fallback
+        # latent kernel: explicit splits of whole 64-token rounds, whose 32-token chunks go to two
+        # token groups in turn; a group's reference is the max of its first chunk, and a score
+        # more than 64 above it sends the whole split to the fallback. In every split of every
+        # unit some head of one group goes well beyond.
+        assert n_tok > 128  # not the one-round kernel
         per = -(-n_tok // splits)
-        st = -(-per // 32) * 32
-        over = max(float((sc[:, :, b:b + st].max(axis=2) - sc[:, :, b:b + 32].max(axis=2)).max())
-                   for b in range(0, n_tok, st))
-        assert over > 64.0, over
+        st = -(-per // 64) * 64
+        chunks = sc.reshape(units, H, n_tok // 32, 32).max(axis=3)
+        for b in range(0, n_tok // 32, st // 32):
+            own = chunks[:, :, b:b + st // 32]
+            over = np.max([(own[:, :, g::2].max(axis=2) - own[:, :, g]).max(axis=1)
+                           for g in (0, 1)], axis=0)
+            assert over.min() > 80.0, over
     else:
         # grouped-query kernel: the running max moves (a rescale) when a later 32-token chunk
         # outgrows it by more than 8; every chunk outgrows the previous one by more than that,
@@ -207,12 +216,13 @@ def test_attention_wide_score_range(kind, H, splits, units):
         assert (cmax[:, :, 1:] - cmax[:, :, :-1]).min() > 8.0
         assert n_tok >= 2 * 32 * 4
     dev = torch.device("cuda:0")
-    ad = attn_desc(w, splits)
+    ad = attn_desc(w, splits, flags)
     ws = torch.empty(hs.hisparse_decode_workspace_bytes(units, k, R, ad), dtype=torch.uint8,
                      device=dev)
     q_d = torch.from_numpy(q.view(np.int16)).to(dev)
     out = decode_pool(torch.from_numpy(pool.view(np.int16)).to(dev), n_rec, w, q_d,
-                      torch.from_numpy(idx).to(dev), ws, splits, units=units).cpu().numpy()
+                      torch.from_numpy(idx).to(dev), ws, splits, units=units,
+                      flags=flags).cpu().numpy()
     for u in range(units):
         ref = oracle_unit(w, q[u], pool[u], idx[u])
         err, rl2 = np.abs(out[u] - ref).max(), rel_l2(out[u], ref)
@@ -223,5 +233,5 @@ def test_attention_wide_score_range(kind, H, splits, units):
     idx_p = inv[idx].astype(np.int32)
     out_p = decode_pool(torch.from_numpy(np.ascontiguousarray(pool[:, perm]).view(np.int16)).to(dev),
                         n_rec, w, q_d, torch.from_numpy(idx_p).to(dev), ws, splits,
-                        units=units).cpu().numpy()
+                        units=units, flags=flags).cpu().numpy()
     assert out.tobytes() == out_p.tobytes()

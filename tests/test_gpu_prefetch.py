@@ -412,7 +412,7 @@ def test_merge_carried_replay_equals_separate(cfg, fetch, share):
 def test_carries_replay_hint_equals_separate(requests):
     """The overlap schedule with HISPARSE_ATTN_CARRIES_REPLAY on the replay-carrying attention
     calls and on their merges, the last layer's attention without it (one or two requests of 128
-    latent heads, k = 2048: one token group per workgroup, where the hint halves the splits):
+    latent heads, k = 2048: up to four workgroup columns, where the hint halves the splits):
     outputs bit-identical to the same plans' attention issued apart from the replay, caches
     byte-identical."""
     G = 4

@@ -46,10 +46,14 @@ DEFER = hs.HISPARSE_ATTN_DEFER_MERGE
     ("mla", 20, 2049, 1, 0, 129, 0),
     ("mla", 40, 2048, 1, 1, 1, 0), ("mla", 40, 2049, 1, 1, 1, 0), ("mla", 20, 2048, 1, 1, 1, 0),
     ("mla", 72, 1024, 1, 1, 2, 0), ("mla", 20, 1025, 1, 1, 2, 0),
-    # grouped-query, one to four head waves: one split (five rounds), and one more
+    # grouped-query, one, two and four head waves: one split (five rounds), and one more
     ("gqa", 4, 640, 1, 0, 2, 0), ("gqa", 4, 641, 1, 0, 2, 0), ("gqa", 16, 40, 16, 0, 2, 0),
     ("gqa", 17, 320, 1, 0, 2, 0), ("gqa", 32, 321, 1, 0, 2, 0), ("gqa", 33, 160, 1, 0, 2, 0),
     ("gqa", 64, 161, 1, 0, 2, 0), ("gqa", 70, 3, 64, 0, 2, 0), ("gqa", 5, 1, 1, 0, 2, 0),
+    # grouped-query beside a fetch, six rounds per split: up to five, one split of more, two splits
+    ("gqa", 4, 640, 1, 0, 2, BESIDE), ("gqa", 4, 1535, 1, 0, 2, BESIDE), ("gqa", 4, 96, 16, 0, 2, BESIDE),
+    ("gqa", 4, 1537, 1, 0, 2, BESIDE), ("gqa", 24, 767, 1, 0, 2, BESIDE), ("gqa", 24, 769, 1, 0, 2, BESIDE),
+    ("gqa", 40, 383, 1, 0, 2, BESIDE), ("gqa", 40, 385, 1, 0, 2, BESIDE), ("gqa", 40, 6, 64, 3, 2, BESIDE),
     ("gqa", 8, 2048, 1, 1, 1, 0), ("gqa", 8, 2049, 1, 1, 1, 0), ("gqa", 8, 1024, 1, 1, 1, 0),
     ("gqa", 256, 2048, 1, 0, 65, 0), ("gqa", 256, 2049, 1, 0, 65, 0),
 ])
