@@ -146,22 +146,25 @@ typedef struct {
 #define HISPARSE_ATTN_DEFER_MERGE 1
 /* hisparse_attn_desc_t.flags, a scheduling hint: the call runs beside
  * another stream's host-link fetch (e.g. two micro-batches taking turns on the link), whose slow
- * host reads occupy the memory pipelines of the CUs they run on. The plan then takes fewer, longer
- * splits (latent attention: half a workgroup per CU instead of one; grouped-query records: at
- * least six rounds of a workgroup's waves per split): the fetch's waves find CUs without an
- * attention workgroup, and the split partial results shrink; on a GPU of its own the call is
- * slower that way. Results differ only within rounding (other split boundaries); each plan is
- * deterministic. */
+ * host reads occupy the memory pipelines of the CUs they run on. Unless num_splits asks for a number
+ * of splits, the plan then takes fewer, longer ones: latent attention aims at half a workgroup per CU
+ * instead of one; grouped-query calls of more than five rounds of a workgroup's waves (128 tokens per
+ * round up to 16 heads, 64 up to 32, 32 above) take at least six rounds per split. The fetch's waves
+ * find CUs without an attention workgroup, and the split partial results shrink; on a GPU of its own
+ * the call is slower that way. Set it on the call and on its hisparse_attention_merge (or
+ * _merge_prefetch) alike. Results differ only within rounding (other split boundaries); each plan
+ * is deterministic. */
 #define HISPARSE_ATTN_BESIDE_FETCH 2
 /* hisparse_attn_desc_t.flags, a scheduling hint for latent attention: the call carries an
  * exact-prefetch replay (hisparse_sparse_decode_prefetch, _part) whose host-link transfer takes
  * longer than the attention itself, so the launch lasts as long as the replay and the merge that
- * follows it sits on the decode chain (Section 3.5). With one token group per workgroup (few
- * workgroup columns, e.g. one request of 128 heads) the plan then takes splits of at least 4
- * chunks instead of 2: half the attention workgroups, which stay hidden behind the replay and
- * leave it more CUs, and half the split partials for the merge to read. Set it on the carrying
- * call and on its hisparse_attention_merge (or _merge_prefetch). Results differ only within
- * rounding (other split boundaries); each plan is deterministic. */
+ * follows it sits on the decode chain (Section 3.5). With fewer than 16 workgroup columns (one per
+ * unit and 64 heads, or 32 if there are no more) and at least 64 rounds of 64 tokens in all, the plan
+ * then takes splits of at least two rounds: half the attention workgroups, which stay hidden behind
+ * the replay and leave it more CUs, and half the split partials for the merge to read. From 5 columns
+ * on the plan does so by itself in calls of more than four rounds, so there the hint changes nothing.
+ * Set it on the carrying call and on its hisparse_attention_merge (or _merge_prefetch). Results differ
+ * only within rounding (other split boundaries); each plan is deterministic. */
 #define HISPARSE_ATTN_CARRIES_REPLAY 4
 
 /* Human-readable name of a status code (static storage). */

@@ -246,7 +246,10 @@ __device__ inline void lds_barrier() {
 // rows: 64 units of 16 heads took 81 us that way, 39 this way). Inside a block, piece p
 // of row r sits in 16-byte slot p ^ tile_swizzle(r): any 16 consecutive rows then place the same
 // piece in 16 different slots of the 256 bytes that all 64 banks serve (row parity picks the
-// half), and so do the transpose reads' row sets.
+// half). A transpose read's 16-lane group has rows of one parity, 4 apart, in the 128 bytes of one
+// half; the latent kernel's two groups of 32 lanes share that half and take each read's banks twice.
+// Counted (SQ_LDS_BANK_CONFLICT per wave and chunk): latent 128 of 555 LDS cycles, two for each
+// transpose read (padded rows: none of 401); grouped-query 32 of 156 (padded rows: 64 of 151).
 template <int P>
 struct Tile {
   static_assert(P % 8 == 0, "whole 128-byte segments");
@@ -704,10 +707,9 @@ void attn_partial_kernel(AttnArgs a) {
 
 // Logical row r of a 32-token MFMA tile -> LDS tile row (token) for the latent-attention kernel.
 // With r = 16a + 8b + 4h + s the row is 16a + 4s + 2b + h: the P operand of a lane (k-step a,
-// half h) then comes straight from its S^T accumulator, and each group of 16 lanes of a V
-// transpose read touches rows 4 apart, i.e. four row bases 16 banks apart under the padded
-// stride, so those reads are free of bank conflicts; the 16 K rows one operand load reads are
-// a permutation of 16 consecutive rows, which are conflict-free as well.
+// half h) then comes straight from its S^T accumulator, and each group of 16 lanes of a V transpose
+// read touches rows 4 apart, which the swizzle spreads over the slots of their half (see Tile); the
+// 16 K rows that one operand load reads are a permutation of 16 consecutive rows.
 __device__ inline int mla_row(int r) {
   return 16 * (r >> 4) + 4 * (r & 3) + 2 * ((r >> 3) & 1) + ((r >> 2) & 1);
 }
@@ -779,8 +781,8 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 // once for its HW head waves; the split's 32-token chunks alternate between the groups, and the
 // two groups' results are merged in LDS at the end, so a workgroup writes one partial result
 // for twice the tokens of one group (half the partial traffic of two workgroups).
-// Bound: a round (one chunk per group) takes 2.0 us with the GPU to itself, 0.9 of them MFMA
-// issue, 0.35 softmax and the rest waiting for the next chunk, of which LDS holds only one (four
+// Bound: a round (one chunk per group) of a 128-head call takes 2.0 us with the GPU to itself, 0.9 of
+// them MFMA issue, 0.35 softmax and the rest waiting for the next chunk, of which LDS holds only one (four
 // tiles of 36 KB fill it). Many workgroups of 16-32 heads reach the HBM rate instead (64 units x
 // 16 heads: 6.3 TB/s in the loop); calls of few rounds are bound by the chain of index, first
 // chunk, result and merge. Measured, merge included, before these tiles -> now: 96 units x 128

@@ -23,7 +23,8 @@
 //   Bound: latency, a chain of five dependent global round trips (selection, page table, recency
 //   index beside it, slot map, tables) and three scans; 16 units, k 2048, B 4096: 8.8 us per call
 //   (12.0 with scans by LDS permutes and the index read entry by entry at phase 3), 1 unit, k 128,
-//   B 512: 6.1 us (8.9).
+//   B 512: 6.1 us (8.9), with tables and selections in the caches; after 1 GiB of other writes the
+//   first takes 3.2 us less than before as well (16.0 against 19.2 between events around the call).
 // fetch_kernel: copies each planned record from the pinned host pool (zero-copy 16-byte
 //   loads through the mapped address) into its slot. The grid is small: a fixed budget of
 //   one-wave workgroups shared by the launch's units, each thread keeping one transfer block
