@@ -247,7 +247,7 @@ __device__ inline void lds_barrier() {
 // of row r sits in 16-byte slot p ^ tile_swizzle(r): any 16 consecutive rows then place the same
 // piece in 16 different slots of the 256 bytes that all 64 banks serve (row parity picks the
 // half). A transpose read's 16-lane group has rows of one parity, 4 apart, in the 128 bytes of one
-// half; the latent kernel's two groups of 32 lanes share that half and take each read's banks twice.
+// half; the latent kernel's two groups of 32 lanes share it and take each read's banks twice.
 // Counted (SQ_LDS_BANK_CONFLICT per wave and chunk): latent 128 of 555 LDS cycles, two for each
 // transpose read (padded rows: none of 401); grouped-query 32 of 156 (padded rows: 64 of 151).
 template <int P>
@@ -781,13 +781,14 @@ __device__ __forceinline__ void mla_split_exact(const AttnArgs& a, const int32_t
 // once for its HW head waves; the split's 32-token chunks alternate between the groups, and the
 // two groups' results are merged in LDS at the end, so a workgroup writes one partial result
 // for twice the tokens of one group (half the partial traffic of two workgroups).
-// Bound: a round (one chunk per group) of a 128-head call takes 2.0 us with the GPU to itself, 0.9 of
-// them MFMA issue, 0.35 softmax and the rest waiting for the next chunk, of which LDS holds only one (four
-// tiles of 36 KB fill it). Many workgroups of 16-32 heads reach the HBM rate instead (64 units x
-// 16 heads: 6.3 TB/s in the loop); calls of few rounds are bound by the chain of index, first
-// chunk, result and merge. Measured, merge included, before these tiles -> now: 96 units x 128
-// heads x 2048 tokens 137 -> 87.5 us, 64 x 16 81 -> 40.8, 16 x 128 33.5 -> 28.2 (of which 67 MB of
-// partials written and read are 13), 5 x 72 x 1337 26.0 -> 17.3, 1 x 128 19.0 -> 16.7.
+// Bound: a round (one chunk per group) of a 128-head call takes 1.7 us with 64 workgroups on the
+// chip and 2.3 with 192 or 256, 0.9 of them MFMA issue, 0.35 softmax and the rest waiting for the
+// next chunk, of which LDS holds only one (four tiles of 36 KB fill it). Many workgroups of 16-32
+// heads reach the HBM rate instead (64 units x 16 heads: 6.3 TB/s in the loop); calls of few rounds
+// are bound by the chain of index, first chunk, result and merge. Measured, merge included, before
+// these tiles -> now: 96 units x 128 heads x 2048 tokens 137 -> 87.5 us, 64 x 16 81 -> 40.8, 16 x 128
+// 33.5 -> 28.2 (of which 67 MB of partials written and read are 13), 5 x 72 x 1337 26.0 -> 17.3, 1 x
+// 128 19.0 -> 16.7.
 //   S^T[token][head] = K[token][:] . Q^T[:][head]   v_mfma_f32_32x32x16_bf16, 36 k-steps, K rows
 //                                                   from LDS, Q resident in VGPRs
 //   O[head][dim]    += P[head][token] . V[token][dim]  v_mfma_f32_32x32x16_bf16, 2 k-steps x 16
@@ -1467,7 +1468,7 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     splits = std::max(1, std::min({splits, max_splits, min_work_splits}));
     // A grouped-query unit of one split needs no merge, a launch of its own that costs about 2.5
     // us, against about 1 us for a round: 11 units x 501 tokens, four rounds, take 8.7 us in one
-    // split against 10.8 in two to four. (A latent round takes 2 us: one request of 33 heads over
+    // split against 10.8 in two to four. (A latent round is longer: one request of 33 heads over
     // 150 tokens takes 11.7 us in three splits of one round and a merge, 13.9 in one of three.)
     if (!is_mla(*attn) && max_splits <= 5) splits = 1;
   }
