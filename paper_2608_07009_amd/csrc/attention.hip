@@ -1387,14 +1387,17 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // splits, 64 units x 2048 tokens 44.9 against 40.8). Up to one workgroup per CU it takes 9.2 to
     // 10.7 us for any number of heads, the tiled kernel 9.7 to 23.7 (1 unit of 128 heads x 128 tokens
     // 9.2 against 11.8, 32 units 10.6 against 23.7). Beyond that its workgroups, which hold a CU's LDS
-    // each for 16 heads, queue: 48 units of 128 heads x 64 tokens 19.3 against 13.7. With up to 16 heads
-    // the tiled kernel has as many workgroups (300 units x 96 tokens 20.1 against 24.3).
+    // each for 16 heads, queue: 48 units of 128 heads x 64 tokens 19.3 against 13.7. And a replay that
+    // the launch carries needs a CU per unit besides: share groups of 28 units of 128 heads x 64
+    // tokens take 66 us against 76 with 32 CUs left, 32 units 95 against 79 with none. With up to 16
+    // heads the tiled kernel has as many workgroups (300 units x 96 tokens 20.1 against 24.3).
+    const int head_blocks = (H + 15) / 16;
     p.rows = p.n_tok <= 4 * kChunk &&
-             (H <= 16 || (int64_t)units * ((H + 15) / 16) <= kTargetWorkgroups);
+             (H <= 16 || (int64_t)units * (head_blocks + 1) <= kTargetWorkgroups);
     p.hw = H <= 32 || p.rows ? 1 : 2;
     p.tg = p.rows ? 1 : 2;
     p.tw = p.rows ? 4 : 1;
-    p.hb = p.rows ? (H + 15) / 16 : (H + 32 * p.hw - 1) / (32 * p.hw);
+    p.hb = p.rows ? head_blocks : (H + 32 * p.hw - 1) / (32 * p.hw);
   } else {              // up to 64 heads per workgroup, 16 per wave
     p.hw = H > 32 ? 4 : (H > 16 ? 2 : 1);
     p.tw = 4 / p.hw;
