@@ -1447,6 +1447,12 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // 1.552 with six, 1.561 with twelve; of 32 x 4 x 4096: 6.107, 6.105, 6.128).
     const bool beside = attn->flags & HISPARSE_ATTN_BESIDE_FETCH;
     int split_rounds = is_mla(*attn) ? 1 : (beside ? 6 : (p.tw == 4 ? 2 : 4));
+    // A carried replay runs on the CUs the attention leaves; a grouped-query call that would leave
+    // fewer than a quarter takes four rounds too (share groups of four layers, 32 units of 4 heads x
+    // 2048 tokens in pages of 16: 357 us with a workgroup on every CU, 304 on half of them).
+    if (!is_mla(*attn) && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY) &&
+        per_split * std::min(splits, p.n_tok / (split_rounds * chunk)) > kTargetWorkgroups * 3 / 4)
+      split_rounds = std::max(split_rounds, 4);
     const int rounds = (p.n_tok + chunk - 1) / chunk;
     const bool few_columns = is_mla(*attn) && per_split < 16;
     if (few_columns && per_split > 4 && rounds > 4) split_rounds = 2;

@@ -54,6 +54,8 @@ DEFER = hs.HISPARSE_ATTN_DEFER_MERGE
     ("gqa", 4, 640, 1, 0, 2, BESIDE), ("gqa", 4, 1535, 1, 0, 2, BESIDE), ("gqa", 4, 96, 16, 0, 2, BESIDE),
     ("gqa", 4, 1537, 1, 0, 2, BESIDE), ("gqa", 24, 767, 1, 0, 2, BESIDE), ("gqa", 24, 769, 1, 0, 2, BESIDE),
     ("gqa", 40, 383, 1, 0, 2, BESIDE), ("gqa", 40, 385, 1, 0, 2, BESIDE), ("gqa", 40, 6, 64, 3, 2, BESIDE),
+    # grouped-query with the replay hint: three quarters of the CUs, and more
+    ("gqa", 4, 2048, 1, 0, 24, CARRY), ("gqa", 4, 2048, 1, 0, 32, CARRY), ("gqa", 16, 1024, 1, 0, 64, CARRY),
     ("gqa", 8, 2048, 1, 1, 1, 0), ("gqa", 8, 2049, 1, 1, 1, 0), ("gqa", 8, 1024, 1, 1, 1, 0),
     ("gqa", 256, 2048, 1, 0, 65, 0), ("gqa", 256, 2049, 1, 0, 65, 0),
 ])
