@@ -162,7 +162,8 @@ typedef struct {
  * heads, or 32 if there are no more) and at least 64 rounds of 64 tokens in all, the plan then takes
  * splits of at least two rounds: half the attention workgroups, which stay hidden behind the replay
  * and leave it more CUs, and half the split partials for the merge to read. From 5 columns on the
- * plan does so by itself in calls of more than four rounds, so there the hint changes nothing.
+ * plan does so by itself in calls of more than four rounds, so there the hint changes nothing more.
+ * Latent calls of up to 32 heads aim at half a workgroup per CU.
  * Grouped-query calls of up to 16 heads that would leave the replay fewer than a quarter of the CUs
  * take splits of at least four rounds of 128 tokens. Set it on the carrying call and on its
  * hisparse_attention_merge (or _merge_prefetch). Results differ only within rounding (other split

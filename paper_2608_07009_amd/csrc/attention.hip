@@ -47,6 +47,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunk = 32;            // tokens per wave per iteration
 constexpr int kTargetWorkgroups = 256;
+// A carried replay keeps to the CUs the attention leaves if there are this many at least. On fewer, a
+// workgroup or two per unit would copy everything: 16 units of 16 heads x 1024 tokens, which leave
+// none, took 462 us for a share group of four layers, 222 with the replay's full grid behind the
+// attention's (in the order of block indices it starts as CUs come free).
+constexpr int kMinIdle = 64;
 constexpr int kMaxSplitRecords = 2048;  // record indices of one split staged in LDS
 // Rescale the running output only when a head's running max grows by more than this (log2
 // units): exponentials are taken against a slightly stale max (values up to 2^8), which is
@@ -1414,8 +1419,12 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
   // (16 units of 128 heads, 2 token groups, 4 splits) that fetch moves 51.9 GB/s against 50.6
   // with a workgroup per CU, the step 1.692 against 1.735 ms, and the split partials halve;
   // the attention itself takes 58 against 40 us, hidden behind the other micro-batch's fetch.
-  const int target = (is_mla(*attn) && (attn->flags & HISPARSE_ATTN_BESIDE_FETCH))
-                         ? kTargetWorkgroups / 2 : kTargetWorkgroups;
+  // So does a latent call of one head wave that carries a replay, which then runs on the other half
+  // (share groups of four layers, 16 units of 32 heads x 1024 tokens: 200 us against 232).
+  const bool half_grid =
+      is_mla(*attn) && ((attn->flags & HISPARSE_ATTN_BESIDE_FETCH) ||
+                        (p.hw == 1 && (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY)));
+  const int target = half_grid ? kTargetWorkgroups / 2 : kTargetWorkgroups;
   // Beside another stream's fetch and with more than 16 workgroup columns (more than 8 units of
   // 128 heads, two token groups) the call hides behind the other micro-batch's longer fetch,
   // whose host reads then set the step; there every workgroup loading its query together with
@@ -1553,10 +1562,11 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
   AttnArgs a{};
   if (prefetch && prefetch->units > 0 && prefetch->n_layers > 0) {
     // on the CUs the attention leaves idle (a workgroup of these kernels holds a CU's LDS, so
-    // replay and attention never share a CU's memory pipeline)
+    // replay and attention never share a CU's memory pipeline); with few or none, as many workgroups
+    // as the threads asked for make, which follow the attention's
     const int64_t n_attn = (int64_t)units * p.n_wg_splits * p.hb;
     const int64_t idle = std::max<int64_t>(0, kTargetWorkgroups - ((n_attn + 7) & ~7LL));
-    if (!carried_replay(*prefetch, 64 * p.hw * p.tg * p.tw, idle,
+    if (!carried_replay(*prefetch, 64 * p.hw * p.tg * p.tw, idle >= kMinIdle ? idle : kTargetWorkgroups,
                         prefetch_threads, prefetch_block_bytes, &a.rp))
       return hipErrorInvalidValue;
   }
