@@ -457,3 +457,57 @@ def test_carries_replay_hint_equals_separate(requests):
         torch.cuda.synchronize()
         split.close()
         apart.close()
+
+
+@pytest.mark.parametrize("cfg,flags,over", [
+    # CUs the attention leaves to the replay: none, fewer than 64, half, more than half
+    (2, 0, dict(num_requests=16, q_heads=32, k=1024, B=2048)),
+    (2, 0, dict(num_requests=24, q_heads=16, k=1024, B=2048)),
+    (2, hs.HISPARSE_ATTN_CARRIES_REPLAY, dict(num_requests=16, q_heads=32, k=1024, B=2048)),
+    (2, 0, dict(num_requests=8, q_heads=128, k=128, B=256)),
+    (3, 0, dict(num_requests=16)),
+    (3, hs.HISPARSE_ATTN_CARRIES_REPLAY, dict(num_requests=16)),
+])
+def test_decode_prefetch_beside_any_grid(cfg, flags, over):
+    """However many CUs the attention leaves, a launch that carries a replay gives the caches and
+    outputs of the two issued apart (the replay as a whole, and in two parts)."""
+    G = 3
+    k = over.get("k", W.workload(cfg).k)
+    w = W.workload(cfg, num_layers=G, share_group=G, L=6 * k, window=k // 8, carry=k // 2, **over)
+    steps = 2
+    log(f"test_decode_prefetch_beside_any_grid {w.name} units={w.units} H={w.q_heads} k={w.k} "
+        f"flags={flags}")
+    fused, apart = Run(w, steps), Run(w, steps)
+    dev = fused.dev
+    ad = attn_desc(w, 0, flags)
+    nb = hs.hisparse_decode_workspace_bytes(w.units, w.k, w.record_bytes, ad)
+    ws = torch.empty(nb, dtype=torch.uint8, device=dev)
+    out_f = torch.empty((G, w.units, w.q_heads, w.d_v), dtype=torch.float32, device=dev)
+    out_a = torch.empty_like(out_f)
+    try:
+        for t in range(steps):
+            q = [torch.from_numpy(W.queries(w, t, l).view(np.int16)).to(dev) for l in range(G)]
+            for r in (fused, apart):
+                hs.hisparse_resolve(r.cache.handle, 0, r.sel_ptr(t, 0), r.slots[0], r.counts[0],
+                                    r.stream)
+            h = fused.cache.handle
+            hs.hisparse_sparse_decode_prefetch(h, 0, q[0], fused.slots[0], out_f[0], ad, ws, nb,
+                                               0, 1, 1, fused.stream)
+            for l, lo, hi in ((0, 0, 100), (1, 100, 256)):
+                hs.hisparse_sparse_decode_prefetch_part(h, l, q[l], fused.slots[0], out_f[l], ad, ws,
+                                                        nb, 0, 2, 1, lo, hi, fused.stream)
+            hs.hisparse_sparse_decode(h, 2, q[2], fused.slots[0], out_f[2], ad, ws, nb,
+                                      fused.stream)
+            hs.hisparse_prefetch_layers(apart.cache.handle, 0, 1, G - 1, apart.stream)
+            for l in range(G):
+                hs.hisparse_sparse_decode(apart.cache.handle, l, q[l], apart.slots[0], out_a[l],
+                                          ad, ws, nb, apart.stream)
+            torch.cuda.synchronize()
+            assert torch.equal(out_f, out_a), f"step {t}"
+            for l in range(G):
+                assert (layer_cache_host(fused, l) == layer_cache_host(apart, l)).all(), \
+                    f"step {t} layer {l}"
+    finally:
+        torch.cuda.synchronize()
+        fused.close()
+        apart.close()
