@@ -159,10 +159,10 @@ typedef struct {
  * (hisparse_sparse_decode_prefetch, _part) whose host-link transfer takes longer than the attention
  * itself, so the launch lasts as long as the replay and the merge that follows it sits on the decode
  * chain (Section 3.5). In latent attention with fewer than 16 workgroup columns (one per unit and 64
- * heads, or 32 if there are no more) and at least 64 rounds of 64 tokens in all, the plan then takes
- * splits of at least two rounds: half the attention workgroups, which stay hidden behind the replay
- * and leave it more CUs, and half the split partials for the merge to read. From 5 columns on the
- * plan does so by itself in calls of more than four rounds, so there the hint changes nothing more.
+ * heads, or 32 if there are no more), more than 256 tokens per unit and at least 2048 over all units,
+ * the plan then takes splits of at least two rounds of 64 tokens: half the attention workgroups, which
+ * stay hidden behind the replay and leave it more CUs, and half the split partials for the merge to
+ * read. From 5 columns on the plan does so by itself, so there the hint changes nothing more.
  * Latent calls of up to 32 heads aim at half a workgroup per CU.
  * Grouped-query calls of up to 16 heads that would leave the replay fewer than a quarter of the CUs
  * take splits of at least four rounds of 128 tokens. Set it on the carrying call and on its

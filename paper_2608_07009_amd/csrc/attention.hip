@@ -1470,10 +1470,10 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // 128 heads with a replay of its 2048 selections into the next shared layer: 16 four-chunk
     // splits instead of 32 two-chunk ones take the launch from 28.0 to 27.4 us and its merge
     // from 5.8 to 4.6 us (one 1M-token request, 56 layers in groups of 4: decode step 2.299 ->
-    // 2.226 ms), although that attention alone takes longer. Not with fewer than 64 one-round
-    // workgroups: their merge is short anyway (2 units of 33 heads x 256 tokens, call and merge: 12.0
-    // against 13.6 us).
-    if (few_columns && per_split * (p.n_tok / chunk) >= 64 &&
+    // 2.226 ms), although that attention alone takes longer. Not where the replay is short: share
+    // groups of four layers, 1 unit of 128 heads x 1999 tokens 95.3 us with the hint, 90.0 without, 3
+    // x 64 x 610 84.1 and 79.9; but 2 x 64 x 1480 95.7 and 99.5.
+    if (few_columns && rounds > 4 && (int64_t)units * p.n_tok >= 2048 &&
         (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
       split_rounds = 2;
     // Whole splits of that many rounds at least. A short call takes one more for what is left over
@@ -1523,9 +1523,9 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
 //  - every smaller number of units; above one workgroup column per CU a unit takes the fewest splits
 //    there are, so the needs to look at are those up to that many units and the call's own;
 //  - the needs without a hint, for the numbers of units up to the last one whose plan it leaves
-//    alone; for all of them unless the call is one it is made for: latent, more than 32 heads. Where
-//    it does lower the need, a part per 1024 records of each unit still covers smaller calls
-//    without it.
+//    alone; for all of them unless the call is one it is made for: latent, more than 32 heads, at
+//    least 64 one-round workgroups. Where it does lower the need, a part per 1024 records of each
+//    unit still covers smaller calls without it.
 // Calls are checked against their own need, never against this.
 size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_bytes,
                                  const hisparse_attn_desc_t* attn) {
@@ -1540,10 +1540,13 @@ size_t attention_workspace_bytes(int32_t units, int32_t top_k, int32_t record_by
   size_t bytes = 0;
   bool without_hint = false;
   for (int32_t u = units; u >= 1; u = std::min(u - 1, columns)) {
-    if (plan_attention(u, top_k, record_bytes, attn, &p) != HISPARSE_OK ||
+    if (plan_attention(u, top_k, record_bytes, attn, &p) != HISPARSE_OK) continue;
+    bare = p;
+    if (plain.flags != attn->flags &&
         plan_attention(u, top_k, record_bytes, &plain, &bare) != HISPARSE_OK)
       continue;
-    const bool hinted = is_mla(*attn) && H > 32 && p.n_parts != bare.n_parts;
+    const bool hinted = is_mla(*attn) && H > 32 && p.n_parts != bare.n_parts &&
+                        (int64_t)u * p.hb * (p.n_tok / (2 * kChunk)) >= 64;
     without_hint = without_hint || !hinted;
     bytes = std::max(bytes, p.workspace_bytes);
     if (without_hint) bytes = std::max(bytes, bare.workspace_bytes);
