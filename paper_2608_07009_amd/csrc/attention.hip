@@ -48,8 +48,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kChunk = 32;            // tokens per wave per iteration
 constexpr int kTargetWorkgroups = 256;
 // A carried replay keeps to the CUs the attention leaves if there are this many at least. On fewer, a
-// workgroup or two per unit would copy everything: 16 units of 16 heads x 1024 tokens, which leave
-// none, took 462 us for a share group of four layers, 222 with the replay's full grid behind the
+// workgroup or two per unit would copy everything: 16 units of 16 heads x 1024 tokens that left
+// none took 462 us for a share group of four layers, 222 with the replay's full grid behind the
 // attention's (in the order of block indices it starts as CUs come free).
 constexpr int kMinIdle = 64;
 constexpr int kMaxSplitRecords = 2048;  // record indices of one split staged in LDS
@@ -1389,9 +1389,9 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
     // At most 128 tokens, the grouped-query kernel's shape: 16 heads per workgroup, four waves on a
     // chunk each, merged in the workgroup, no merge launch. One round is all it does well: its
     // tiles leave no room for the next chunk (16 heads, 256 tokens 12.2 us against 11.5 in four
-    // splits, 64 units x 2048 tokens 44.9 against 40.8). Up to one workgroup per CU it takes 9.2 to
-    // 10.7 us for any number of heads, the tiled kernel 9.7 to 23.7 (1 unit of 128 heads x 128 tokens
-    // 9.2 against 11.8, 32 units 10.6 against 23.7). Beyond that its workgroups, which hold a CU's LDS
+    // splits, 64 units x 2048 tokens 44.9 against 40.8). Up to 224 workgroups it takes 9.2 to 10.4
+    // us for any number of heads, the tiled kernel 9.7 to 21.6 (1 unit of 128 heads x 128 tokens 9.2
+    // against 11.8, 24 units 10.2 against 19.8). Past a CU each its workgroups, which hold a CU's LDS
     // each for 16 heads, queue: 48 units of 128 heads x 64 tokens 19.3 against 13.7. And a replay that
     // the launch carries needs a CU per unit besides: share groups of 28 units of 128 heads x 64
     // tokens take 66 us against 76 with 32 CUs left, 32 units 95 against 79 with none. With up to 16
@@ -1477,9 +1477,9 @@ hisparse_status_t plan_attention(int32_t units, int32_t top_k, int32_t record_by
         (attn->flags & HISPARSE_ATTN_CARRIES_REPLAY))
       split_rounds = 2;
     // Whole splits of that many rounds at least. A short call takes one more for what is left over
-    // instead of longer ones (5 units of 32 heads x 320 tokens, two rounds per split: 14.0 us in three, 16.1
-    // in two of three rounds); in longer calls, and in those that fill the grid, it is not worth its partials
-    // (4 units of 64 heads x 900 tokens: 15.8 us in 8 splits, 17.4 in 15).
+    // instead of longer ones (5 units of 32 heads x 320 tokens, two rounds per split: 14.0 us in
+    // three, 16.1 in two of three rounds); in longer calls, and in those that fill the grid, it is
+    // not worth its partials (4 units of 64 heads x 900 tokens: 15.8 us in 8 splits, 17.4 in 15).
     const int min_work_splits = few_columns && rounds <= 8
                                     ? (rounds + split_rounds - 1) / split_rounds
                                     : std::max(1, p.n_tok / (split_rounds * chunk));
@@ -1569,8 +1569,9 @@ hipError_t launch_attention(const AttnPlan& p, const hisparse_attn_desc_t& attn,
     // as the threads asked for make, which follow the attention's
     const int64_t n_attn = (int64_t)units * p.n_wg_splits * p.hb;
     const int64_t idle = std::max<int64_t>(0, kTargetWorkgroups - ((n_attn + 7) & ~7LL));
-    if (!carried_replay(*prefetch, 64 * p.hw * p.tg * p.tw, idle >= kMinIdle ? idle : kTargetWorkgroups,
-                        prefetch_threads, prefetch_block_bytes, &a.rp))
+    if (!carried_replay(*prefetch, 64 * p.hw * p.tg * p.tw,
+                        idle >= kMinIdle ? idle : kTargetWorkgroups, prefetch_threads,
+                        prefetch_block_bytes, &a.rp))
       return hipErrorInvalidValue;
   }
   a.idx_units = idx_units > 0 ? idx_units : units;
